@@ -159,6 +159,37 @@ int dbg_shrink_at()
 #endif
 }
 
+// float -> f16 bits, round to nearest even, for |f| < 65504 (values of the
+// split weights); f16 bits -> float.
+uint16_t host_f2h(float f)
+{
+    uint32_t u;
+    std::memcpy(&u, &f, 4);
+    const uint16_t sign = (uint16_t)((u >> 16) & 0x8000u);
+    u &= 0x7fffffffu;
+    if (u >= 0x38800000u)  // 2^-14 and up: rebias the exponent, round 13 bits off
+        return (uint16_t)(sign | ((u - 0x38000000u + 0xfffu + ((u >> 13) & 1u)) >> 13));
+    // below: multiples of 2^-24, the spacing of floats in [0.5, 1)
+    float a;
+    std::memcpy(&a, &u, 4);
+    a += 0.5f;
+    std::memcpy(&u, &a, 4);
+    return (uint16_t)(sign | (u - 0x3f000000u));
+}
+
+float host_h2f(uint16_t h)
+{
+    const uint32_t m = h & 0x7fffu;
+    float f;
+    if (m >= 0x400u) {
+        const uint32_t u = (m << 13) + 0x38000000u;
+        std::memcpy(&f, &u, 4);
+    } else {
+        f = (float)m * 0x1p-24f;
+    }
+    return (h & 0x8000u) ? -f : f;
+}
+
 uint16_t host_f2bf(float f)
 {
     uint32_t u;
@@ -181,6 +212,12 @@ struct NetLayer {
     int nbt = 0;          // channel blocks, padded to a multiple of nb * wn
     int ksteps = 0;
     size_t w_off = 0, b_off = 0;  // offsets into the net's device block
+    // Half-step walk (c_in a multiple of 16).  bf16: vec layers whose c_in is
+    // an odd multiple of 16 (w_off is in its order).  float32: layers whose
+    // inputs a tanh bounds also keep their weights split into f16 pairs.
+    bool hs = false;
+    int ksteps_h = 0;             // float32: K steps of 32 (bf16: ksteps counts them already)
+    size_t ws_off = 0, bs_off = 0, us_off = 0;  // split weights, scaled bias, unscale factors
     bool has_w32 = false;         // OIHW float32 copy for the direct kernel
     size_t w32_off = 0;
 };
@@ -211,6 +248,9 @@ struct fs_net {
 
 namespace {
 
+// Split float32 layers: inputs in [-1, 1] times this fill the f16 range.
+constexpr float kSplitInScale = 32768.f;
+
 int kstep_of(int dtype) { return dtype == DT_BF16 ? 32 : 16; }
 int elem_of(int dtype) { return dtype == DT_BF16 ? 2 : 4; }
 
@@ -234,34 +274,94 @@ int chan_of(const NetLayer &l, int dtype, int blk, int row)
     return 32 * p + 8 * g + 4 * h + e;
 }
 
+// K index of element (lane group g, e) of half-step walk step s: its tap and
+// input channel (tap past the kernel: zero weight).
+void half_step_k(const NetLayer &l, int s, int g, int e, int &tap, int &ci)
+{
+    const int nh = l.cin / 16, h = 2 * s + g / 2;
+    tap = h / nh;
+    ci = (h % nh) * 16 + (g % 2) * 8 + e;
+}
+
+// Float32 weights as f16 pairs for the half-step walk: [step][block][high,
+// low][64 lanes][8], each output channel's weights first multiplied by the
+// power of two that brings its largest to [2^14, 2^15): then hi = the nearest
+// f16 and lo = the nearest f16 of the rest keep 23 significand bits of every
+// weight within 2^-16 of the largest.  unscale takes scale and the inputs'
+// scale in_scale back off the sums.  False (layer stays float32) when a value
+// is not finite or a channel's range does not fit.
+bool pack_split_weights(const NetLayer &l, const float *w, const float *bias, float in_scale,
+                        std::vector<uint16_t> &out, std::vector<float> &bs, std::vector<float> &us)
+{
+    const size_t K = (size_t)l.cin * l.k * l.kx;
+    bs.assign((size_t)l.nbt * 16, 0.f);
+    us.assign((size_t)l.nbt * 16, 1.f);
+    const int taps = l.k * l.kx;
+    out.assign((size_t)l.ksteps_h * l.nbt * 2 * 64 * 8, 0);
+    std::vector<std::pair<int, int>> at((size_t)l.ksteps_h * 32);  // (weight index, packed index) of K index k
+    for (int s = 0, n = 0; s < l.ksteps_h; ++s)
+        for (int g = 0; g < 4; ++g)
+            for (int e = 0; e < 8; ++e) {
+                int tap, ci;
+                half_step_k(l, s, g, e, tap, ci);
+                at[n++] = {tap < taps ? ci * taps + tap : -1, (s * l.nbt * 128 + g * 16) * 8 + e};
+            }
+    for (int co = 0; co < l.cout; ++co) {
+        const float *wc = w + co * K;
+        float m = 0.f;
+        for (size_t i = 0; i < K; ++i) {
+            const float a = std::fabs(wc[i]);
+            if (!(a <= 3.4e38f)) return false;
+            m = std::max(m, a);
+        }
+        int e = 0;
+        if (m > 0.f) (void)std::frexp(m, &e);  // m in [2^(e-1), 2^e)
+        if (e < -60 || e > 60) return false;
+        const float scale = std::ldexp(1.f, 15 - e);
+        us[co] = 1.f / (scale * in_scale);
+        bs[co] = bias[co] * scale * in_scale;
+        if (!(std::fabs(bs[co]) <= 1e36f)) return false;
+        uint16_t *dst = out.data() + ((size_t)(co / 16) * 128 + co % 16) * 8;
+        for (const auto &[from, to] : at) {
+            if (from < 0) continue;
+            const float v = wc[from] * scale;
+            const uint16_t hi = host_f2h(v);
+            dst[to] = hi;
+            dst[to + 64 * 8] = host_f2h(v - host_h2f(hi));
+        }
+    }
+    return true;
+}
+
 void pack_conv_weights(const NetLayer &l, const float *w, int dtype, std::vector<uint8_t> &out)
 {
     const int KSTEP = kstep_of(dtype), LPE = KSTEP / 4, es = elem_of(dtype);
     const size_t n = (size_t)l.ksteps * l.nbt * 64 * LPE;
     out.assign(n * es, 0);
     const int taps = l.k * l.kx;
+    const size_t K = (size_t)l.cin * taps;
+    std::vector<int> chan(l.nbt * 16);
+    for (int r = 0; r < l.nbt * 16; ++r) chan[r] = chan_of(l, dtype, r / 16, r % 16);
     for (int s = 0; s < l.ksteps; ++s)
-        for (int nb = 0; nb < l.nbt; ++nb)
-            for (int lane = 0; lane < 64; ++lane)
-                for (int e = 0; e < LPE; ++e) {
-                    const int g = lane / 16, nn = lane % 16;
-                    const int co = chan_of(l, dtype, nb, nn);
-                    int tap, ci;
-                    if (l.vec) {
-                        const int ncc = l.cin / KSTEP;
-                        tap = s / ncc;
-                        ci = (s % ncc) * KSTEP + g * LPE + e;
-                    } else {
-                        const int kk = s * KSTEP + g * LPE + e;
-                        tap = kk / l.cin;
-                        ci = kk % l.cin;
-                    }
-                    float v = 0.f;
-                    if (co < l.cout && tap < taps) {
-                        const int dy = tap / l.kx, dx = tap % l.kx;
-                        v = w[(((size_t)co * l.cin + ci) * l.k + dy) * l.kx + dx];
-                    }
-                    const size_t idx = (((size_t)s * l.nbt + nb) * 64 + lane) * LPE + e;
+        for (int g = 0; g < 4; ++g)
+            for (int e = 0; e < LPE; ++e) {
+                int tap, ci;
+                if (dtype == DT_BF16 && l.hs) {
+                    half_step_k(l, s, g, e, tap, ci);
+                } else if (l.vec) {
+                    const int ncc = l.cin / KSTEP;
+                    tap = s / ncc;
+                    ci = (s % ncc) * KSTEP + g * LPE + e;
+                } else {
+                    const int kk = s * KSTEP + g * LPE + e;
+                    tap = kk / l.cin;
+                    ci = kk % l.cin;
+                }
+                if (tap >= taps) continue;
+                for (int r = 0; r < l.nbt * 16; ++r) {
+                    if (chan[r] >= l.cout) continue;
+                    const float v = w[chan[r] * K + (size_t)ci * taps + tap];
+                    const size_t idx = (((size_t)s * l.nbt + r / 16) * 64 + g * 16 + r % 16) * LPE + e;
                     if (dtype == DT_BF16) {
                         const uint16_t h = host_f2bf(v);
                         std::memcpy(&out[idx * 2], &h, 2);
@@ -269,6 +369,7 @@ void pack_conv_weights(const NetLayer &l, const float *w, int dtype, std::vector
                         std::memcpy(&out[idx * 4], &v, 4);
                     }
                 }
+            }
 }
 
 // Optional tile override for tuning sweeps:
@@ -338,7 +439,7 @@ struct Launch {
     PoolArgs pool;
     HeadArgs head;
     int mb = 0, nb = 0, wn = 1, wk = 1;
-    bool vec = false, has_fc = false;
+    bool vec = false, hs = false, has_fc = false;
     bool direct = false;      // vector-ALU convolution for tiny K
     int frag_tiles = 0, frag_lds = 0;  // per-fragment tiling when run tiles are planned
     int gx = 1, gy = 1;
@@ -401,7 +502,7 @@ void plan_run_tiles(const NetLayer &l, const Geo &in, int mt, int cs, int es, in
                     Launch &L)
 {
     if (const char *e = getenv("FRAGSCAN_RUN"); e && e[0] == '0') return;
-    if (!conv_tile_supported(L.mb, l.nb, l.wn, l.wk, l.vec, true)) return;
+    if (!conv_tile_supported(L.mb, l.nb, l.wn, l.wk, l.vec, l.hs, true)) return;
     const int ky = l.k, kx = l.kx;
     if (in.Qy > kMaxAxis || in.Qx > kMaxAxis) return;
     long long sy = 0, sx = 0;
@@ -443,7 +544,9 @@ void plan_run_tiles(const NetLayer &l, const Geo &in, int mt, int cs, int es, in
 // Tile choice for a conv launch (the tiling itself is described in conv_impl.h).
 // wide: the float32 4 x 13 tile of conv_f32_wide.hip (l.nb = 13, l.wn = 1),
 // which has no entry in the shared tile lists.
-fs_status plan_conv_tiles(const fs_net *net, const NetLayer &l, const Geo &in, Launch &L, bool wide = false)
+// packed: no padding between the pixels in LDS (a window that fits only so).
+fs_status plan_conv_tiles(const fs_net *net, const NetLayer &l, const Geo &in, Launch &L, bool wide = false,
+                          bool packed = false)
 {
     const int ky = l.k, kx = l.kx;
     const int hout_max = in.hmax - ky + 1, wout_max = in.wmax - kx + 1;
@@ -451,7 +554,7 @@ fs_status plan_conv_tiles(const fs_net *net, const NetLayer &l, const Geo &in, L
     const int KSTEP = kstep_of(net->dtype);
     // pixel stride in LDS: +16 bytes per pixel spreads 16 consecutive pixels'
     // 16-byte reads over distinct banks (FRAGSCAN_LDS_PAD overrides, elements)
-    int pad = 16 / es;
+    int pad = packed ? 0 : 16 / es;
     if (const char *e = getenv("FRAGSCAN_LDS_PAD")) pad = atoi(e);
     if (l.vec && (pad * es) % 16) pad = 16 / es;
     const int cs = l.vec ? l.cin + pad : l.cin;
@@ -475,7 +578,7 @@ fs_status plan_conv_tiles(const fs_net *net, const NetLayer &l, const Geo &in, L
     const int mbs[4] = {4, 2, 1, 8};
     for (int mi = 0; mi < 4; ++mi) {
         const int mb = mb_force ? mb_force : mbs[mi];
-        if (wide ? mb != 4 : !conv_tile_supported(mb, l.nb, l.wn, l.wk, l.vec)) {
+        if (wide ? mb != 4 : !conv_tile_supported(mb, l.nb, l.wn, l.wk, l.vec, l.hs)) {
             if (mb_force) break;
             continue;
         }
@@ -537,8 +640,8 @@ fs_status plan_conv_tiles(const fs_net *net, const NetLayer &l, const Geo &in, L
             if (rows_t && need_r <= kMaxLdsBytes) {
                 auto per_cu = [&](size_t need) {
                     if (net->ncu > 0)
-                        return conv_blocks_per_cu(net->dtype, in.is_image, mb, l.nb, l.wn, l.wk, l.vec, false,
-                                                  (int)need);
+                        return conv_blocks_per_cu(net->dtype, in.is_image, mb, l.nb, l.wn, l.wk, l.vec, l.hs,
+                                                  false, (int)need);
                     return (int)std::min<size_t>(8, kMaxLdsBytes / need);
                 };
                 auto weight = [](int n) { return n <= 1 ? 1.30 : n == 2 ? 1.02 : 1.0; };
@@ -606,12 +709,13 @@ Geo pool_geo(const Geo &g, int ky, int kx, int sy, int sx)
 // filter; a tile holds pool_rt filter rows, i.e. (pool_rt + kpy - 1) x
 // (band + kpx - 1) convolution outputs, which must fit the register tile (mt
 // pixels).
-fs_status plan_conv_pool_tiles(const fs_net *net, const NetLayer &l, const Geo &in, int kpy, int kpx, Launch &L)
+fs_status plan_conv_pool_tiles(const fs_net *net, const NetLayer &l, const Geo &in, int kpy, int kpx, Launch &L,
+                               bool packed = false)
 {
     const int ky = l.k, kx = l.kx;
     const int es = elem_of(net->dtype);
     const int KSTEP = kstep_of(net->dtype);
-    const int pad = 16 / es;
+    const int tpad = 16 / es, pad = packed ? 0 : tpad;
     const int cs = l.vec ? l.cin + pad : l.cin;
     const int offtab = l.vec ? 0 : (int)align_up((size_t)l.ksteps * KSTEP * 4, 16);
     const int hM_max = in.hmax - ky + 1 - kpy + 1, wM_max = in.wmax - kx + 1 - kpx + 1;
@@ -621,7 +725,7 @@ fs_status plan_conv_pool_tiles(const fs_net *net, const NetLayer &l, const Geo &
     const int mbs[4] = {4, 8, 2, 1};
     for (int mi = 0; mi < 4; ++mi) {
         const int mb = mb_force ? mb_force : mbs[mi];
-        if (!conv_tile_supported(mb, l.nb, l.wn, l.wk, l.vec)) {
+        if (!conv_tile_supported(mb, l.nb, l.wn, l.wk, l.vec, l.hs)) {
             if (mb_force) break;
             continue;
         }
@@ -635,7 +739,7 @@ fs_status plan_conv_pool_tiles(const fs_net *net, const NetLayer &l, const Geo &
             const int rt = std::min(mt / ew - (kpy - 1), hmax);
             if (rt < 1) continue;  // narrower bands
             const size_t win = offtab + (size_t)(rt + kpy - 1 + ky - 1) * (ew + kx - 1) * cs * es;
-            const size_t tile = (size_t)mt * (l.wn * l.nb * 16 + pad) * es;
+            const size_t tile = (size_t)mt * (l.wn * l.nb * 16 + tpad) * es;
             const size_t part = (size_t)(l.wk - 1) * (4 / l.wk) * mb * l.nb * 4 * 64 * 4;
             const size_t need = std::max(std::max(win, tile), part);
             if (win > 96 * 1024 || need > kMaxLdsBytes) {
@@ -742,7 +846,7 @@ fs_status make_plan(const fs_net *net, int B, int H, int W, Plan &P, const View 
     int cur = -1;  // where the current activations live
     size_t buf = 0;
     for (int li = 0; li < body; ++li) {
-        const NetLayer &l = net->L[li];
+        NetLayer l = net->L[li];
         Launch L{};
         L.layer = li;
         L.n_layers = 1;
@@ -801,7 +905,24 @@ fs_status make_plan(const fs_net *net, int B, int H, int W, Plan &P, const View 
             o.hmax = *std::max_element(o.ey.begin(), o.ey.end());
             o.wmax = *std::max_element(o.ex.begin(), o.ex.end());
             L.type = 0;
+            // Float32 layers with split weights take the f16 matrix cores
+            // (the half-step walk): per 16 x 16 outputs and 32 K indices,
+            // three products of 16 cycles instead of eight of 32.  N4 on
+            // 8 x 1024^2: 5x5 48 -> 48 6.95 -> 2.38 ms, 4x4 4.62 and 4.57 ->
+            // 1.77 and 1.72, FC1 + head 9.70 -> 3.11; FRAGSCAN_SPLIT=0 keeps
+            // the float32 products.
+            if (net->dtype == DT_F32 && l.hs) {
+                const char *sp = getenv("FRAGSCAN_SPLIT");
+                bool any = false;
+                int mbf = 0;
+                tile_override(li, &mbf, nullptr, nullptr, nullptr);
+                for (int m : {1, 2, 4, 8})
+                    any = any || ((!mbf || m == mbf) && conv_tile_supported(m, l.nb, l.wn, l.wk, true, true));
+                l.hs = any && l.ksteps_h >= l.wk && !(sp && sp[0] == '0');
+                if (l.hs) l.ksteps = l.ksteps_h;
+            }
             L.vec = l.vec;
+            L.hs = l.hs;
             L.nb = l.nb;
             L.wn = l.wn;
             L.wk = l.wk;
@@ -838,8 +959,16 @@ fs_status make_plan(const fs_net *net, int B, int H, int W, Plan &P, const View 
                 L.direct = true;
                 L.conv.lds_bytes = 0;
             } else {
-                fs_status st = pool_fuse ? plan_conv_pool_tiles(net, l, g, net->L[li + 1].k, net->L[li + 1].kx, L)
-                                         : plan_conv_tiles(net, l, g, L);
+                fs_status st = FS_OK;
+                // (bf16 layers with an odd multiple of 16 input channels
+                // could do without the padding before they took the vector
+                // path: their largest windows still can)
+                for (bool packed : {false, true}) {
+                    if (packed && !(net->dtype == DT_BF16 && l.hs)) break;
+                    st = pool_fuse ? plan_conv_pool_tiles(net, l, g, net->L[li + 1].k, net->L[li + 1].kx, L, packed)
+                                   : plan_conv_tiles(net, l, g, L, false, packed);
+                    if (st == FS_OK) break;
+                }
                 if (st != FS_OK) return st;
                 // The float32 FC layer with the fused head on a grid that
                 // runs it one workgroup per CU (the rule below), with 14
@@ -851,18 +980,22 @@ fs_status make_plan(const fs_net *net, int B, int H, int W, Plan &P, const View 
                 if (fused_here && !pool_fuse && net->dtype == DT_F32 && l.vec && l.nb == 7 && l.wn == 2 &&
                     l.wk == 1 && l.nbt == 14 && l.cout <= 13 * 16) {
                     const long long tiles = (long long)B * F * a.nbands * (a.run ? L.frag_tiles : a.tiles_per_band);
-                    bool wide = net->ncu > 0 && tiles <= 12LL * net->ncu &&
-                                conv_blocks_per_cu(net->dtype, g.is_image, L.mb, l.nb, l.wn, l.wk, l.vec, false,
+                    bool wide = net->ncu > 0 && !l.hs && tiles <= 12LL * net->ncu &&
+                                conv_blocks_per_cu(net->dtype, g.is_image, L.mb, l.nb, l.wn, l.wk, l.vec, false, false,
                                                    a.lds_bytes) == 2;
                     if (const char *e = getenv("FRAGSCAN_WIDE"); e && e[0]) wide = e[0] == '1';
                     if (wide) {
                         NetLayer lw = l;
                         lw.nb = 13;
                         lw.wn = 1;
+                        lw.hs = false;
+                        lw.ksteps = net->L[li].ksteps;
                         Launch Lw = L;
                         Lw.nb = 13;
                         Lw.wn = 1;
                         Lw.conv.run = 0;
+                        Lw.hs = false;
+                        Lw.conv.ksteps = lw.ksteps;
                         if (plan_conv_tiles(net, lw, g, Lw, true) == FS_OK) L = Lw;
                     }
                 }
@@ -883,12 +1016,12 @@ fs_status make_plan(const fs_net *net, int B, int H, int W, Plan &P, const View 
                     // (N4 on 512x512 and 2x512x512 images; 3-5% slower on
                     // larger grids; other layers, whose tiles fit three,
                     // 12-18% slower): pad its LDS to admit one.
-                    if (fused_here && net->ncu > 0 && (long long)gx * L.gy <= 12LL * net->ncu &&
-                        conv_blocks_per_cu(net->dtype, g.is_image, L.mb, L.nb, L.wn, L.wk, L.vec, run, lds) == 2)
+                    if (fused_here && !L.hs && net->ncu > 0 && (long long)gx * L.gy <= 12LL * net->ncu &&
+                        conv_blocks_per_cu(net->dtype, g.is_image, L.mb, L.nb, L.wn, L.wk, L.vec, L.hs, run, lds) == 2)
                         lds = std::max(lds, (int)(kMaxLdsBytes / 2 + 1024));
                     // plan-only nets: 256 CUs, one workgroup each
                     const int bpc = net->ncu > 0 ? conv_blocks_per_cu(net->dtype, g.is_image, L.mb, L.nb, L.wn,
-                                                                      L.wk, L.vec, run, lds) : 1;
+                                                                      L.wk, L.vec, L.hs, run, lds) : 1;
                     const long long slots = (long long)(net->ncu > 0 ? net->ncu : 256) * std::max(bpc, 1);
                     return ((long long)gx * L.gy + slots - 1) / slots;
                 };
@@ -919,7 +1052,7 @@ fs_status make_plan(const fs_net *net, int B, int H, int W, Plan &P, const View 
             L.bytes = (double)B * in_pix * g.C * (g.is_image ? 4 : es) + (double)L.out_pixels * l.cout * es +
                       (double)l.cin * ky * kx * l.cout * es;
             L.name = L.direct ? conv_direct_kernel_name(net->dtype, g.is_image, l.cin, ky * kx)
-                              : conv_kernel_name(net->dtype, g.is_image, L.mb, L.nb, L.wn, L.wk, L.vec, a.run);
+                              : conv_kernel_name(net->dtype, g.is_image, L.mb, L.nb, L.wn, L.wk, L.vec, L.hs, a.run);
             if (pool_fuse) {
                 const int kpy = net->L[li + 1].k, kpx = net->L[li + 1].kx;
                 if (g.Qy * kpy > kMaxAxis || g.Qx * kpx > kMaxAxis)
@@ -1082,7 +1215,7 @@ std::string planner_env()
                                        "FRAGSCAN_NO_FUSED_HEAD", "FRAGSCAN_RUN", "FRAGSCAN_ROWTILES",
                                        "FRAGSCAN_STORE", "FRAGSCAN_LDS_PAD", "FRAGSCAN_WIDE",
                                        "FRAGSCAN_POOL_ROWS", "FRAGSCAN_XSIB",
-                                       "FRAGSCAN_SWAP"};
+                                       "FRAGSCAN_SWAP", "FRAGSCAN_SPLIT"};
     std::string sig;
     for (const char *v : vars) {
         const char *e = getenv(v);
@@ -1251,6 +1384,12 @@ hipError_t enqueue(const fs_net *net, const Plan &P, const float *d_image, float
         L.conv.out = ptr(L.dst);
         L.conv.w = mem + l.w_off;
         L.conv.bias = reinterpret_cast<const float *>(mem + l.b_off);
+        if (L.hs && net->dtype == DT_F32) {
+            L.conv.w = mem + l.ws_off;
+            L.conv.bias = reinterpret_cast<const float *>(mem + l.bs_off);
+            L.conv.unscale = reinterpret_cast<const float *>(mem + l.us_off);
+            L.conv.in_scale = kSplitInScale;
+        }
         if (L.conv.head_ncls > 0) {
             L.conv.head_w = reinterpret_cast<const float *>(mem + net->head_wp_off);
             L.conv.head_wbf = net->has_head_wbf ? mem + net->head_wbf_off : nullptr;
@@ -1261,7 +1400,7 @@ hipError_t enqueue(const fs_net *net, const Plan &P, const float *d_image, float
         if (L.direct)
             return launch_conv_direct(L.conv, reinterpret_cast<const float *>(mem + l.w32_off), net->dtype,
                                       L.in_f32, L.gx, s);
-        return launch_conv(L.conv, net->dtype, L.in_f32, L.mb, L.nb, L.wn, L.wk, L.vec, L.gx, L.gy, s);
+        return launch_conv(L.conv, net->dtype, L.in_f32, L.mb, L.nb, L.wn, L.wk, L.vec, L.hs, L.gx, L.gy, s);
     }
     if (L.type == 1) {
         L.pool.in = ptr(L.src);
@@ -1489,14 +1628,24 @@ static fs_status net_create(const fs_layer *layers, int32_t n_layers, int32_t in
         // staging, which the gather path does
         l.vec = (l.cin % KSTEP) == 0 && !(dtype == FS_BF16 && i == 0);
         const int nbt0 = (l.cout + 15) / 16;
+        if (dtype == FS_BF16 && i > 0 && l.cin % 32 == 16) {
+            // an odd multiple of 16 input channels: the half-step walk, where
+            // its tile shape has an instance
+            int nb = 1, wn = 1, wk = 1;
+            choose_channel_tile(nbt0, true, &nb, &wn);
+            tile_override(i, nullptr, &nb, &wn, nullptr, &wk);
+            for (int mb : {1, 2, 4, 8}) l.hs = l.hs || conv_tile_supported(mb, nb, wn, wk, true, true);
+            l.vec = l.hs;
+        }
         choose_channel_tile(nbt0, l.vec, &l.nb, &l.wn);
         // narrow channel tiles with a long K walk: two waves split K so each
         // wave owns 4 pixel blocks (more products per operand load, measured
         // faster on the 48 -> 48 layers of N4) without a larger LDS window
-        l.wk = (l.vec && l.wn == 1 && l.nb == 3 && l.k * l.kx * l.cin >= 16 * 16) ? 2 : 1;
+        // (bf16 layers on the half-step walk: 0-20% slower split, N4 on 512^2)
+        l.wk = (l.vec && !l.hs && l.wn == 1 && l.nb == 3 && l.k * l.kx * l.cin >= 16 * 16) ? 2 : 1;
         tile_override(i, nullptr, &l.nb, &l.wn, nullptr, &l.wk);
         bool any = false;
-        for (int mb : {1, 2, 4, 8}) any = any || conv_tile_supported(mb, l.nb, l.wn, l.wk, l.vec);
+        for (int mb : {1, 2, 4, 8}) any = any || conv_tile_supported(mb, l.nb, l.wn, l.wk, l.vec, l.hs);
         if (!any) {
             delete net;
             return fail(FS_ERR_UNSUPPORTED, "layer %d: no convolution tile with %d x %d channel blocks", i,
@@ -1504,7 +1653,7 @@ static fs_status net_create(const fs_layer *layers, int32_t n_layers, int32_t in
         }
         const int grp = l.nb * l.wn;
         l.nbt = (nbt0 + grp - 1) / grp * grp;
-        l.ksteps = l.vec ? l.k * l.kx * (l.cin / KSTEP) : (l.k * l.kx * l.cin + KSTEP - 1) / KSTEP;
+        l.ksteps = (l.k * l.kx * l.cin + KSTEP - 1) / KSTEP;
         if (l.ksteps < l.wk) {  // every K-splitting wave needs at least one step
             delete net;
             return fail(FS_ERR_UNSUPPORTED, "layer %d: %d K steps cannot be split over %d waves", i, l.ksteps, l.wk);
@@ -1519,6 +1668,30 @@ static fs_status net_create(const fs_layer *layers, int32_t n_layers, int32_t in
             if (co < l.cout) bp[r] = bias[co];
         }
         l.b_off = push(bp.data(), bp.size() * 4);
+        // Inputs a tanh bounds to [-1, 1] (pools in between keep the bound):
+        // the layer's products can run on the f16 matrix cores, inputs and
+        // weights split into two f16 values each.  Nets that return their
+        // scores (no softmax) keep the float32 products and so their map bit
+        // for bit: scores can be far smaller than the terms they are summed
+        // from, and relative to them the two roundings differ by up to 1e-5
+        // (the largest of 200 seeded N4 nets; from float64 the split ones
+        // are 6.6e-6 off, the float32 ones 8.7e-6), where probabilities
+        // differ by 2e-7.  FRAGSCAN_SPLIT=1 takes the split there too.
+        int prev = i - 1;
+        while (prev >= 0 && L[prev].kind == FS_MAXPOOL) --prev;
+        const char *sp = getenv("FRAGSCAN_SPLIT");
+        const bool want_split = sp && sp[0] ? sp[0] == '1' : L.back().act == FS_ACT_SOFTMAX;
+        if (dtype == FS_F32 && want_split && prev >= 0 && L[prev].act == FS_ACT_TANH && l.cin % 16 == 0 && l.cin <= 256) {
+            std::vector<uint16_t> wsp;
+            std::vector<float> bs, us;
+            l.ksteps_h = (l.k * l.kx * (l.cin / 16) + 1) / 2;
+            if (pack_split_weights(l, s.weight, bias.data(), kSplitInScale, wsp, bs, us)) {
+                l.hs = true;
+                l.ws_off = push(wsp.data(), wsp.size() * 2);
+                l.bs_off = push(bs.data(), bs.size() * 4);
+                l.us_off = push(us.data(), us.size() * 4);
+            }
+        }
         if (!l.vec && conv_direct_supported(l.cin, l.k * l.kx, l.cout)) {
             // [rows][KP] copy for the direct kernel, K index (dy * k_x + dx) * c_in + ci,
             // then the biases in channel order
@@ -1777,8 +1950,8 @@ fs_status fs_scan_launches(const fs_net *net, int32_t B, int32_t H, int32_t W, f
         if (L.type == 0 && !L.direct) {
             o.lds_bytes = L.conv.lds_bytes;
             if (net->ncu > 0)
-                o.per_cu = conv_blocks_per_cu(net->dtype, L.in_f32, L.mb, L.nb, L.wn, L.wk, L.vec, L.conv.run,
-                                              L.conv.lds_bytes);
+                o.per_cu = conv_blocks_per_cu(net->dtype, L.in_f32, L.mb, L.nb, L.wn, L.wk, L.vec, L.hs,
+                                              L.conv.run, L.conv.lds_bytes);
         }
     }
     return FS_OK;

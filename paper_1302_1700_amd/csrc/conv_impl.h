@@ -38,6 +38,22 @@
 //     channels at a time, and a lane's A operand is one 16-byte LDS read.
 //     Gather path (small c_in, e.g. the first layer): K = (tap, channel)
 //     flattened and padded to KSTEP, gathered through an LDS offset table.
+//     Half steps (HS; c_in a multiple of 16): a K step of 32 takes two
+//     16-channel groups of the (tap, group) sequence, which may lie at two
+//     taps, lanes g < 2 the first, g >= 2 the second.  bf16 layers with 16 or
+//     48 channels need no gather that way (N4 in bf16 on 512 x 512: 514 ->
+//     185 us a scan).  Float32 layers whose inputs a tanh bounds run on the
+//     f16 matrix cores there: x = hi + lo and w = hi + lo as f16 pairs (scaled
+//     by powers of two; 23 significand bits each), hi hi + hi lo + lo hi
+//     accumulated in float32.  The float32 products cap a layer at 157
+//     TFLOP/s, three f16 products at a third of the 1135 the f16 matrix
+//     cores reach in a large library product: the 5x5 48 -> 48 layer of N4
+//     on 8 x 1024^2 went from 136 to 395 TFLOP/s.  Against float64 the split
+//     is the more accurate: 64 to 1216 terms of tanh values and N(0, 1/K)
+//     weights are off by 1.2e-7 to 3.9e-7 (2-norm), float32 products by
+//     1.4e-7 to 6.2e-7 (an eighth as many roundings of the running sum
+//     outweigh the operands' last bit and the dropped lo lo).  The window
+//     holds the pairs in the float32 layout's space.
 //   - Epilogue: bias and tanh in float32, then each lane stores its four
 //     (bf16 with paired channel blocks: eight) consecutive channels of a
 //     pixel straight from its registers (bf16: round to nearest even), only
@@ -113,6 +129,26 @@ __device__ __forceinline__ float tanh_fast(float x)
 {
     const float t = __builtin_amdgcn_exp2f(x * 2.8853900817779268f);  // exp(2x)
     return 1.0f - 2.0f * __builtin_amdgcn_rcpf(t + 1.0f);
+}
+
+// Four float32 values, times a power of two, as two f16 values each: x s =
+// hi + lo with hi the nearest f16 and lo the nearest f16 of what is left, 23
+// of the 24 significand bits.
+typedef _Float16 h2v __attribute__((ext_vector_type(2)));
+typedef _Float16 h8v __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ void split4(u4 x, float s, uint2 &hi, uint2 &lo)
+{
+    float v[4];
+    h2v h[2], l[2];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = __uint_as_float(x[e]) * s;
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        h[p] = __builtin_convertvector(f2v{v[2 * p], v[2 * p + 1]}, h2v);
+        l[p] = __builtin_convertvector(f2v{v[2 * p] - (float)h[p][0], v[2 * p + 1] - (float)h[p][1]}, h2v);
+    }
+    hi = uint2{__builtin_bit_cast(uint32_t, h[0]), __builtin_bit_cast(uint32_t, h[1])};
+    lo = uint2{__builtin_bit_cast(uint32_t, l[0]), __builtin_bit_cast(uint32_t, l[1])};
 }
 
 template <bool BF>
@@ -342,13 +378,21 @@ __device__ __forceinline__ void fused_head_finish(const ConvArgs &a, int b, int 
 // launches wait on memory) are compiled for six workgroups per CU (at most
 // 80 registers: six waves per SIMD instead of five; 4-5% faster on the
 // 2x2 16 -> 16 + pool layers; larger tiles would spill).
-template <int MB, int NB, int WN, int WK, bool BF, bool IN_F32, bool VEC, bool RUN>
-__global__ __launch_bounds__(256, (!BF && NB == 1 && MB <= 4) ? 6 : 1) void conv_frag_mfma(ConvArgs a)
+constexpr int min_blocks(int mb, int nb, bool bf, bool hs)
 {
+    if (!bf && nb == 1 && mb <= 4) return hs ? 4 : 6;
+    return hs && mb * nb >= 24 ? 2 : 1;
+}
+
+template <int MB, int NB, int WN, int WK, bool BF, bool IN_F32, bool VEC, bool RUN, bool HS>
+__global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfma(ConvArgs a)
+{
+    static_assert(!HS || VEC, "half steps walk channel vectors");
+    constexpr bool SPLIT = HS && !BF;  // float32 as two f16 values
     using TC = typename Elem<BF>::T;                                // LDS / operand element
     using TI = typename std::conditional<IN_F32, float, TC>::type;  // global input element
-    constexpr int KSTEP = Elem<BF>::KSTEP;
-    constexpr int LPE = KSTEP / 4;  // elements per lane per K step (16 bytes)
+    constexpr int KSTEP = SPLIT ? 32 : Elem<BF>::KSTEP;
+    constexpr int LPE = 16 / (int)sizeof(TC);  // elements of a 16-byte load
 
     extern __shared__ __align__(16) unsigned char smem[];
 
@@ -516,7 +560,9 @@ __global__ __launch_bounds__(256, (!BF && NB == 1 && MB <= 4) ? 6 : 1) void conv
             const int dr = P / Cc, dc = P - dr * Cc;
             int soff = (gy0 + r) * rowp + __mul24(c0 + c, a.in_c) + v * width;
             const int sstep = dr * rowp + dc * a.in_c, swrap = rowp - Cc * a.in_c;
-            int doff = __mul24(__mul24(row0, Cc) + p, CS) + v * width;
+            // (split: the 16-byte slots 2w, 2w + 1 of a pixel, channels 8w .. 8w + 7,
+            // hold the eight high halves and then the eight low ones)
+            int doff = __mul24(__mul24(row0, Cc) + p, CS) + (SPLIT ? (v >> 1) * 8 + (v & 1) * 2 : v * width);
             const int dstep = P * CS;
             while (p < npx) {
                 decltype(load(0)) val[UN];
@@ -548,13 +594,22 @@ __global__ __launch_bounds__(256, (!BF && NB == 1 && MB <= 4) ? 6 : 1) void conv
                     }
                 }
 #pragma unroll
-                for (int u = 0; u < UN; ++u)
-                    if (dsto[u] >= 0) *reinterpret_cast<decltype(load(0)) *>(win_lds + dsto[u]) = val[u];
+                for (int u = 0; u < UN; ++u) {
+                    if (dsto[u] < 0) continue;
+                    if constexpr (SPLIT) {
+                        uint2 hi, lo;
+                        split4(val[u], a.in_scale, hi, lo);
+                        *reinterpret_cast<uint2 *>(win_lds + dsto[u]) = hi;
+                        *reinterpret_cast<uint2 *>(win_lds + dsto[u] + 4) = lo;
+                    } else {
+                        *reinterpret_cast<decltype(load(0)) *>(win_lds + dsto[u]) = val[u];
+                    }
+                }
             }
         };
         if constexpr (VEC && !IN_F32) {
             const int nvec = a.cin / LPE;
-            if (nvec <= 64) {
+            if (SPLIT || nvec <= 64) {  // (the planner keeps split layers to 64 slots)
                 walk(nvec, LPE, [&](int off) { return *reinterpret_cast<const u4 *>(src + off); });
                 return;
             }
@@ -671,6 +726,9 @@ __global__ __launch_bounds__(256, (!BF && NB == 1 && MB <= 4) ? 6 : 1) void conv
         return FS_DBG_OK(a.dbg, (seg ? q1 : q) < a.nfrag && y < hh && x < ww && y < a.out_h && x < a.out_w,
                          DBG_CONV_WRITE);
     };
+    // a lane's K values within a step: 16 bytes at g, or (half steps) its
+    // 8-channel chunk of the half step g / 2, whose offset differs by half
+    const int klane = HS ? (g & 1) * 8 : g * LPE;
     int abase[MB];
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
@@ -678,9 +736,9 @@ __global__ __launch_bounds__(256, (!BF && NB == 1 && MB <= 4) ? 6 : 1) void conv
         if (m < n0) {
             int y, x;
             dtw.qr(l0 + m, y, x);
-            abase[i] = ((y - yfirst) * Cc + x) * CS + g * LPE;
+            abase[i] = ((y - yfirst) * Cc + x) * CS + klane;
         } else {
-            abase[i] = g * LPE;  // any in-window address; the result is not stored
+            abase[i] = klane;  // any in-window address; the result is not stored
         }
     }
     if (RUN && n1 > 0) {
@@ -690,7 +748,7 @@ __global__ __launch_bounds__(256, (!BF && NB == 1 && MB <= 4) ? 6 : 1) void conv
             if (m >= n0 && m < npix) {
                 int y, x;
                 dtw1.qr(m - n0, y, x);
-                abase[i] = ((y + R) * Cc + x) * CS + g * LPE;
+                abase[i] = ((y + R) * Cc + x) * CS + klane;
             }
         }
     }
@@ -732,7 +790,113 @@ __global__ __launch_bounds__(256, (!BF && NB == 1 && MB <= 4) ? 6 : 1) void conv
         }
     };
 
-    if constexpr (VEC) {
+    // K walk in half steps: a step takes the 16-channel groups 2s (lanes g < 2)
+    // and 2s + 1 (g >= 2) of the sequence (tap, group of 16 channels), so c_in
+    // need only be a multiple of 16 and a step may span two taps; past an odd
+    // end the upper half re-reads the last group against zero weights.
+    // A block's weights are reloaded for the next step right after its
+    // products (one register set), the pixels a step ahead (two).
+    if constexpr (HS) {
+        constexpr int NW = SPLIT ? 2 : 1;  // 16-byte operands per block and per pixel: (high, low) halves
+        auto kwalk = [&](auto nbac) {
+            constexpr int NBA = decltype(nbac)::value;
+            const int nh = a.cin / 16, nhs = a.ky * a.kx * nh;
+            const int s_begin = (a.ksteps * wk) / WK, nsteps = (a.ksteps * (wk + 1)) / WK - s_begin;
+            int hs = 2 * s_begin;
+            int cc = hs % nh, dx = (hs / nh) % a.kx, dy = (hs / nh) / a.kx;
+            const bool upper = g >= 2;
+            auto pos = [&] { return (dy * Cc + dx) * CS + cc * 16; };
+            auto advance = [&] {  // the next half step (stays at the last one)
+                const int more = hs + 1 < nhs;
+                hs += more;
+                cc += more;
+                const int w1 = cc == nh;
+                cc = w1 ? 0 : cc;
+                dx += w1;
+                const int w2 = dx == a.kx;
+                dx = w2 ? 0 : dx;
+                dy += w2;
+            };
+            auto step_off = [&] {
+                const int lo = pos();
+                advance();
+                const int hi = pos();
+                advance();
+                return upper ? hi : lo;
+            };
+            constexpr int PX = MB * NB >= 24 ? 1 : 2;  // pixel register sets (one: reloaded after the step's products)
+            u4 b[NB][NW], av[PX][MB][NW];
+            const size_t wstep_h = (size_t)a.nbt * 64 * NW;
+            const u4 *wnx = reinterpret_cast<const u4 *>(a.w) + (size_t)nb0 * 64 * NW + lane + (size_t)s_begin * wstep_h;
+            auto load_w = [&](const u4 *src, int j) {
+#pragma unroll
+                for (int p = 0; p < NW; ++p) b[j][p] = src[(j * NW + p) * 64];
+            };
+            auto load_px = [&](u4(&v)[MB][NW], int off) {
+#pragma unroll
+                for (int i = 0; i < MB; ++i)
+#pragma unroll
+                    for (int p = 0; p < NW; ++p) v[i][p] = *reinterpret_cast<const u4 *>(win_lds + abase[i] + off + p * LPE);
+            };
+#pragma unroll
+            for (int j = 0; j < NBA; ++j) load_w(wnx, j);
+            const int off0 = step_off();
+            load_px(av[0], off0);
+            auto step = [&](int s, const u4(&x)[MB][NW], u4(&xn)[MB][NW]) {
+                const bool more = s + 1 < nsteps;
+                const int off = step_off();
+                if constexpr (PX == 2) load_px(xn, more ? off : off0);
+                wnx += more ? wstep_h : 0;
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = 0; j < NBA; ++j) {
+                    if constexpr (SPLIT) {
+#pragma unroll
+                        for (int p = 0; p < 3; ++p)  // high * high, high * low, low * high
+#pragma unroll
+                            for (int i = 0; i < MB; ++i)
+                                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                                    __builtin_bit_cast(h8v, b[j][p == 2]), __builtin_bit_cast(h8v, x[i][p == 1]),
+                                    acc[i][j], 0, 0, 0);
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < MB; ++i)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                __builtin_bit_cast(bf8, b[j][0]), __builtin_bit_cast(bf8, x[i][0]), acc[i][j], 0, 0, 0);
+                    }
+                    load_w(wnx, j);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if constexpr (PX == 1) {
+                    load_px(xn, more ? off : off0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            int s = 0;
+            for (; s + 2 <= nsteps; s += 2) {
+                step(s, av[0], av[PX - 1]);
+                step(s + 1, av[PX - 1], av[0]);
+            }
+            if (s < nsteps) step(s, av[0], av[PX - 1]);
+        };
+        if constexpr (WN == 2 && WK == 1 && NB >= 2) {
+            if (nb0 + NB - 1 >= a.nbu)
+                kwalk(std::integral_constant<int, NB - 1>());
+            else
+                kwalk(std::integral_constant<int, NB>());
+        } else {
+            kwalk(std::integral_constant<int, NB>());
+        }
+        if constexpr (SPLIT) {
+            // back from the operands' power-of-two scales (exact)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                const f4 us = *reinterpret_cast<const f4 *>(a.unscale + (nb0 + j) * 16 + 4 * g);
+#pragma unroll
+                for (int i = 0; i < MB; ++i) acc[i][j] *= us;
+            }
+        }
+    } else if constexpr (VEC) {
         auto kwalk = [&](auto nbac) {
             // K step s covers tap (dy, dx) and channels cc*KSTEP ..; the three
             // indices advance incrementally.  Weights are loaded PD steps ahead
@@ -1268,10 +1432,10 @@ __global__ __launch_bounds__(256, (!BF && NB == 1 && MB <= 4) ? 6 : 1) void conv
     }
 }
 
-template <int MB, int NB, int WN, int WK, bool BF, bool IN_F32, bool VEC, bool RUN>
+template <int MB, int NB, int WN, int WK, bool BF, bool IN_F32, bool VEC, bool RUN, bool HS = false>
 hipError_t launch_one(const ConvArgs &a, int gx, int gy, hipStream_t s)
 {
-    auto kern = conv_frag_mfma<MB, NB, WN, WK, BF, IN_F32, VEC, RUN>;
+    auto kern = conv_frag_mfma<MB, NB, WN, WK, BF, IN_F32, VEC, RUN, HS>;
     if (a.lds_bytes > 65536) {
         // the instance may take up to a whole CU's LDS: set once per device
         // (a runtime call per launch cost tens of microseconds of host time)
@@ -1313,33 +1477,54 @@ hipError_t launch_one(const ConvArgs &a, int gx, int gy, hipStream_t s)
 #define FS_CONV_TILES_RUN_GATHER(X) \
     X(2, 1, 1, 1) X(2, 2, 1, 1) X(2, 3, 1, 1) X(2, 4, 1, 1) X(4, 1, 1, 1) X(4, 2, 1, 1)
 
+// Half-step instances (c_in a multiple of 16): float32 layers whose operands
+// are split into f16 pairs, and bf16 layers.
+#define FS_CONV_TILES_HS(X)                                                                     \
+    X(1, 1, 1, 1) X(1, 2, 1, 1) X(1, 3, 1, 1) X(1, 4, 1, 1) X(2, 1, 1, 1) X(2, 2, 1, 1)          \
+    X(2, 3, 1, 1) X(2, 4, 1, 1) X(4, 1, 1, 1) X(4, 2, 1, 1) X(4, 3, 1, 1) X(4, 4, 1, 1)          \
+    X(8, 3, 1, 1) X(2, 7, 1, 1) X(4, 7, 1, 1) X(2, 7, 2, 1) X(4, 7, 2, 1) X(4, 4, 2, 1)          \
+    X(2, 4, 4, 1) X(4, 4, 4, 1) X(2, 3, 1, 2) X(4, 3, 1, 2) X(8, 3, 1, 2) X(8, 3, 1, 4)
+#define FS_CONV_TILES_RUN_HS(X) \
+    X(2, 2, 1, 1) X(4, 2, 1, 1) X(4, 3, 1, 1) X(4, 3, 1, 2) X(4, 4, 1, 1) X(4, 7, 1, 1) X(4, 7, 2, 1)
+
+// The instance of one tile shape, or nullptr.
+template <bool BF, bool IN_F32, bool VEC, bool HS>
+const void *tile_kernel(int mb, int nb, int wn, int wk, bool run)
+{
+#define FS_CONV_PTR(M, N, W, K) \
+    if (mb == M && nb == N && wn == W && wk == K) return reinterpret_cast<const void *>(conv_frag_mfma<M, N, W, K, BF, IN_F32, VEC, false, HS>);
+#define FS_CONV_PTR_RUN(M, N, W, K) \
+    if (mb == M && nb == N && wn == W && wk == K) return reinterpret_cast<const void *>(conv_frag_mfma<M, N, W, K, BF, IN_F32, VEC, true, HS>);
+    if (run) {
+        if constexpr (HS) {
+            FS_CONV_TILES_RUN_HS(FS_CONV_PTR_RUN)
+        } else if constexpr (VEC) {
+            FS_CONV_TILES_RUN_VEC(FS_CONV_PTR_RUN)
+        } else {
+            FS_CONV_TILES_RUN_GATHER(FS_CONV_PTR_RUN)
+        }
+    } else {
+        if constexpr (HS) {
+            FS_CONV_TILES_HS(FS_CONV_PTR)
+        } else if constexpr (VEC) {
+            FS_CONV_TILES_VEC(FS_CONV_PTR)
+        } else {
+            FS_CONV_TILES_GATHER(FS_CONV_PTR)
+        }
+    }
+#undef FS_CONV_PTR
+#undef FS_CONV_PTR_RUN
+    return nullptr;
+}
+
 // Workgroups of one tile shape that fit on a CU with `lds` dynamic LDS bytes
 // (0 if unknown or the shape has no instance): a 256-thread workgroup
 // puts one wave on each of the 4 SIMDs, each SIMD holds 512 VGPRs per lane
 // (allocated in granules of 8), and the CU has kMaxLdsBytes of LDS.
-template <bool BF, bool IN_F32, bool VEC>
+template <bool BF, bool IN_F32, bool VEC, bool HS = false>
 int tile_blocks_per_cu(int mb, int nb, int wn, int wk, bool run, int lds)
 {
-    const void *kern = nullptr;
-#define FS_CONV_OCC(M, N, W, K) \
-    if (mb == M && nb == N && wn == W && wk == K) kern = reinterpret_cast<const void *>(conv_frag_mfma<M, N, W, K, BF, IN_F32, VEC, false>);
-#define FS_CONV_OCC_RUN(M, N, W, K) \
-    if (mb == M && nb == N && wn == W && wk == K) kern = reinterpret_cast<const void *>(conv_frag_mfma<M, N, W, K, BF, IN_F32, VEC, true>);
-    if (run) {
-        if constexpr (VEC) {
-            FS_CONV_TILES_RUN_VEC(FS_CONV_OCC_RUN)
-        } else {
-            FS_CONV_TILES_RUN_GATHER(FS_CONV_OCC_RUN)
-        }
-    } else {
-        if constexpr (VEC) {
-            FS_CONV_TILES_VEC(FS_CONV_OCC)
-        } else {
-            FS_CONV_TILES_GATHER(FS_CONV_OCC)
-        }
-    }
-#undef FS_CONV_OCC
-#undef FS_CONV_OCC_RUN
+    const void *kern = tile_kernel<BF, IN_F32, VEC, HS>(mb, nb, wn, wk, run);
     if (!kern) return 0;
     hipFuncAttributes fa{};
     if (hipFuncGetAttributes(&fa, kern) != hipSuccess) {
@@ -1352,21 +1537,25 @@ int tile_blocks_per_cu(int mb, int nb, int wn, int wk, bool run, int lds)
     return std::min(n, 8);
 }
 
-template <bool BF, bool IN_F32, bool VEC>
+template <bool BF, bool IN_F32, bool VEC, bool HS = false>
 hipError_t dispatch_tile(const ConvArgs &a, int mb, int nb, int wn, int wk, int gx, int gy, hipStream_t s)
 {
 #define FS_CONV_CASE(M, N, W, K) \
-    if (mb == M && nb == N && wn == W && wk == K) return launch_one<M, N, W, K, BF, IN_F32, VEC, false>(a, gx, gy, s);
+    if (mb == M && nb == N && wn == W && wk == K) return launch_one<M, N, W, K, BF, IN_F32, VEC, false, HS>(a, gx, gy, s);
 #define FS_CONV_CASE_RUN(M, N, W, K) \
-    if (mb == M && nb == N && wn == W && wk == K) return launch_one<M, N, W, K, BF, IN_F32, VEC, true>(a, gx, gy, s);
+    if (mb == M && nb == N && wn == W && wk == K) return launch_one<M, N, W, K, BF, IN_F32, VEC, true, HS>(a, gx, gy, s);
     if (a.run) {
-        if constexpr (VEC) {
+        if constexpr (HS) {
+            FS_CONV_TILES_RUN_HS(FS_CONV_CASE_RUN)
+        } else if constexpr (VEC) {
             FS_CONV_TILES_RUN_VEC(FS_CONV_CASE_RUN)
         } else {
             FS_CONV_TILES_RUN_GATHER(FS_CONV_CASE_RUN)
         }
     } else {
-        if constexpr (VEC) {
+        if constexpr (HS) {
+            FS_CONV_TILES_HS(FS_CONV_CASE)
+        } else if constexpr (VEC) {
             FS_CONV_TILES_VEC(FS_CONV_CASE)
         } else {
             FS_CONV_TILES_GATHER(FS_CONV_CASE)

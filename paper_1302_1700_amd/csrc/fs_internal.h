@@ -83,7 +83,9 @@ struct ConvArgs {
     const void *in;       // [nfrag][in_h][in_w][in_c] (float or bf16; first layer: the image)
     void *out;            // [nfrag][out_h][out_w][cout]
     const void *w;        // packed weights (api.hip: pack_conv_weights)
-    const float *bias;    // [nbt * 16] in (block, row) order, zero padded
+    const float *bias;    // [nbt * 16] in (block, row) order, zero padded (split: times the row's scale)
+    const float *unscale; // split: [nbt * 16], 1 / (in_scale * the row's weight scale), powers of two
+    float in_scale;       // split: power of two the staged inputs are multiplied by
     int nfrag;            // B * F
     int F, Qy, Qx;        // fragments per image, per axis
     int in_h, in_w, in_c; // padded input dims; in_c = channel pitch of the input
@@ -182,8 +184,9 @@ struct HeadArgs {
 // operand type; `in_f32` says the input is float32 even in a bf16 net (the
 // image).  Convolution register tiles: mb pixel blocks x nb channel blocks per
 // wave, wn waves across the output channels, wk waves splitting the K steps,
-// 4 / (wn * wk) across the pixels.  a.run picks the run-tile instance.
-hipError_t launch_conv(const ConvArgs &a, int dtype, bool in_f32, int mb, int nb, int wn, int wk, bool vec,
+// 4 / (wn * wk) across the pixels.  a.run picks the run-tile instance, hs the
+// half-step walk (float32: operands split into f16 pairs).
+hipError_t launch_conv(const ConvArgs &a, int dtype, bool in_f32, int mb, int nb, int wn, int wk, bool vec, bool hs,
                        int grid_x, int grid_y, hipStream_t s);
 hipError_t launch_pool(const PoolArgs &a, int dtype, bool in_f32, int grid, hipStream_t s);
 // Mirrored borders: out[B][He][We][C] from in[B][H][W][C], extended index
@@ -197,10 +200,10 @@ hipError_t launch_head(const HeadArgs &a, int dtype, bool in_f32, bool has_fc, i
 // tiles, one workgroup per CU); launch_conv routes that shape there.
 hipError_t launch_conv_f32_wide(const ConvArgs &a, int gx, int gy, hipStream_t s);
 // Whether a tile shape has an instance (run: one with run tiles).
-bool conv_tile_supported(int mb, int nb, int wn, int wk, bool vec, bool run = false);
+bool conv_tile_supported(int mb, int nb, int wn, int wk, bool vec, bool hs, bool run = false);
 // Workgroups of that convolution kernel resident per CU with `lds` bytes of
 // dynamic LDS, on the current device (0 if the query fails).
-int conv_blocks_per_cu(int dtype, bool in_f32, int mb, int nb, int wn, int wk, bool vec, bool run, int lds);
+int conv_blocks_per_cu(int dtype, bool in_f32, int mb, int nb, int wn, int wk, bool vec, bool hs, bool run, int lds);
 // Direct (vector-ALU) convolution for tiny K = c_in * taps (taps = k_y * k_x,
 // K <= 64) and c_out <= 48; wpk = weights as [rows][KP] float32 with rows =
 // c_out rounded up to 8 (zero rows past c_out), K index (dy * k_x + dx) *
@@ -213,7 +216,7 @@ hipError_t launch_conv_direct(const ConvArgs &a, const float *wpk, int dtype, bo
 std::string conv_direct_kernel_name(int dtype, bool in_f32, int cin, int taps);
 
 // Kernel names as the profiler reports them (for measurement reports).
-std::string conv_kernel_name(int dtype, bool in_f32, int mb, int nb, int wn, int wk, bool vec, bool run);
+std::string conv_kernel_name(int dtype, bool in_f32, int mb, int nb, int wn, int wk, bool vec, bool hs, bool run);
 std::string pool_kernel_name(int dtype, bool in_f32, int ky, int kx, int sy, int sx, int C, int rows);
 const char *head_kernel_name(int dtype, bool in_f32, bool has_fc);
 

@@ -685,3 +685,35 @@ def test_stride_rules():
     assert not names[0].endswith("+pool") and names[1].startswith("pool_frag<"), names
 
 
+
+
+def test_half_step_layers(monkeypatch):
+    """Which layers walk K in half steps (the last template argument of the
+    launch name): float32 layers with a multiple of 16 inputs bounded by a
+    tanh, in nets that end in a softmax (FRAGSCAN_SPLIT=1/0 forces either);
+    bf16 layers after the first with an odd multiple of 16.  Sizes, work and
+    workspace are those of the plain walk."""
+    def half(layers, dt, H=200):
+        net = fsb.Net(layers, wl.make_weights(layers, 1, 0.1), layers[0]["c_in"], 0, dt, plan_only=True)
+        ls = net.launches(1, H, H)
+        p = net.plan(1, H, H)
+        net.close()
+        return ({L["layer"] for L in ls if L["name"].split(">")[0].endswith("true")},
+                p, [(L["layer"], L["out_pixels"], L["flops"], L["bytes"]) for L in ls])
+
+    n4 = wl.n4_layers()
+    scores = n4[:-1] + [wl.fc(1, 200, 2, "none")]
+    linear = [wl.conv(2, 1, 16, "none"), wl.conv(2, 16, 32), wl.pool(2, 32), wl.conv(2, 32, 24), wl.conv(1, 24, 16),
+              wl.fc(2, 16, 8), wl.fc(1, 8, 2, "softmax")]
+    monkeypatch.delenv("FRAGSCAN_SPLIT", raising=False)
+    on = half(n4, "f32")
+    assert on[0] == {2, 4, 6, 8}
+    assert half(scores, "f32")[0] == set()
+    assert half(linear, "f32")[0] == {3, 5}  # layer 1 reads a linear layer, layer 4 24 channels
+    assert half(linear, "bf16")[0] == {1, 5}
+    assert half(n4, "bf16")[0] == {2, 4, 6, 8}
+    monkeypatch.setenv("FRAGSCAN_SPLIT", "0")
+    off = half(n4, "f32")
+    assert off[0] == set() and off[1:] == on[1:]
+    monkeypatch.setenv("FRAGSCAN_SPLIT", "1")
+    assert half(scores, "f32")[0] == {2, 4, 6, 8}
