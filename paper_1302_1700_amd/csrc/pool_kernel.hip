@@ -129,22 +129,27 @@ __global__ __launch_bounds__(256) void pool_frag(PoolArgs a)
     }
 }
 
-// Row-band version for pool sizes 2..4 (the common case).  The k x k maxima
-// at every position of the parent, M[y][x] = max_{i,j<k} P[y+i][x+j], are
-// exactly the children's pixels: M[y][x] is pixel (y div k, x div k) of the
-// child with offset (x mod k, y mod k).  A thread owns one (x, channel vector)
+// Row-band version for windows of 2..4 rows and columns, any steps.  The
+// maxima at every position of the parent, M[y][x] = max_{i<ky, j<kx}
+// P[y+i][x+j], are exactly the children's pixels: every window start y lies in
+// one child, M[y][x] being pixel (y div sy, x div sx) of the child with offset
+// (x mod sx, y mod sy) (steps of the window's size: the paper's pools).
+// A thread owns one (x, channel vector)
 // column of a band of RB rows of M: it walks the parent rows once, keeps the
-// last k horizontal maxima in registers, and writes each M row to its child.
-// So a parent element is fetched from memory once (its k horizontal
+// last ky horizontal maxima in registers, and writes each M row to its child.
+// So a parent element is fetched from memory once (its kx horizontal
 // neighbours share it through the cache) and every child row is written with
-// contiguous stores; the k^2 siblings no longer re-read the parent.
-template <int K, int RB, bool BF, bool IN_F32, int V>
+// contiguous stores; the siblings no longer re-read the parent.  Strided
+// pools, which the one-workgroup-per-child-row kernel above took at 1.7-2.4
+// TB/s, run at 6.4 TB/s here (95 -> 24 and 96 -> 35 us: 32 and 48 float32 channels, 3x3 / 2 and
+// 2x2 / 3 pools of 2 x 601 x 517 images).
+template <int KY, int KX, int RB, bool BF, bool IN_F32, int V>
 __global__ __launch_bounds__(256) void pool_frag_rows(PoolArgs a, int nbands, int nchunks, int nblocks)
 {
     using TO = typename std::conditional<BF, uint16_t, float>::type;
     using TI = typename std::conditional<IN_F32, float, TO>::type;
     // Workgroups are dealt to the 8 XCDs round-robin; renumber them so each
-    // XCD takes a contiguous run of bands, and the K - 1 parent rows that
+    // XCD takes a contiguous run of bands, and the KY - 1 parent rows that
     // neighbouring bands share are read from that XCD's L2 rather than twice
     // from HBM (the grid is padded to a multiple of 8; the padding exits).
     int bid = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
@@ -161,31 +166,31 @@ __global__ __launch_bounds__(256) void pool_frag_rows(PoolArgs a, int nbands, in
     const int pi = chunk * 256 + threadIdx.x;
     const int x = pi / nv, cv = pi - (pi / nv) * nv;
     const int y0 = band * RB;
-    const int yend = min(y0 + RB, hp - K + 1);  // M rows [y0, yend)
-    if (x > wp - K || y0 >= yend) return;
+    const int yend = min(y0 + RB, hp - KY + 1);  // M rows [y0, yend)
+    if (x > wp - KX || y0 >= yend) return;
     // the parent rows and columns the thread reads lie inside the parent's true size
-    [[maybe_unused]] const int lastrow = min(y0 + RB + K - 2, hp - 1), lastcol = x + K - 1;
-    if (!FS_DBG_OK(a.dbg, p < a.n_children / (K * K) && lastrow < hp - a.dbg_shrink && lastcol < wp - a.dbg_shrink &&
+    [[maybe_unused]] const int lastrow = min(y0 + RB + KY - 2, hp - 1), lastcol = x + KX - 1;
+    if (!FS_DBG_OK(a.dbg, p < a.n_children / (a.sy * a.sx) && lastrow < hp - a.dbg_shrink && lastcol < wp - a.dbg_shrink &&
                               lastrow < a.in_h && lastcol < a.in_w, DBG_POOL_READ))
         return;
 
     const TI *src = reinterpret_cast<const TI *>(a.in) + (size_t)p * a.in_h * a.in_w * a.C + (size_t)x * a.C + cv * V;
     const size_t prow = (size_t)a.in_w * a.C;
-    const int Qc = a.Qx * K;
-    const size_t cbase = (size_t)b * a.F * K * K;
+    const int Qc = a.Qx * a.sx;
+    const size_t cbase = (size_t)b * a.F * a.sy * a.sx;
     TO *out = reinterpret_cast<TO *>(a.out);
 
-    // The RB + K - 1 parent rows this thread reads, every load issued before
+    // The RB + KY - 1 parent rows this thread reads, every load issued before
     // any maximum is taken (rows past the band's last are clamped to the
     // fragment's last row: in bounds, and unused), so a thread has all its
     // loads in flight at once.
-    u4 raw[RB + K - 1][K];
-    float sc[RB + K - 1][K];
+    u4 raw[RB + KY - 1][KX];
+    float sc[RB + KY - 1][KX];
 #pragma unroll
-    for (int r = 0; r < RB + K - 1; ++r) {
+    for (int r = 0; r < RB + KY - 1; ++r) {
         const TI *row = src + (size_t)min(y0 + r, hp - 1) * prow;
 #pragma unroll
-        for (int j = 0; j < K; ++j) {
+        for (int j = 0; j < KX; ++j) {
             if constexpr (V == 1) {
                 if constexpr (!BF || IN_F32)
                     sc[r][j] = row[(size_t)j * a.C];
@@ -197,13 +202,13 @@ __global__ __launch_bounds__(256) void pool_frag_rows(PoolArgs a, int nbands, in
         }
     }
     // horizontal maxima of each row, then the K-row maxima
-    float h[RB + K - 1][V];
+    float h[RB + KY - 1][V];
 #pragma unroll
-    for (int r = 0; r < RB + K - 1; ++r) {
+    for (int r = 0; r < RB + KY - 1; ++r) {
 #pragma unroll
         for (int e = 0; e < V; ++e) h[r][e] = -INFINITY;
 #pragma unroll
-        for (int j = 0; j < K; ++j) {
+        for (int j = 0; j < KX; ++j) {
             if constexpr (V == 1) {
                 h[r][0] = fmaxf(h[r][0], sc[r][j]);
             } else if constexpr (BF) {
@@ -218,27 +223,31 @@ __global__ __launch_bounds__(256) void pool_frag_rows(PoolArgs a, int nbands, in
             }
         }
     }
-    const int ox = x % K, xbar = x / K;
+    const int xbar = x / a.sx, ox = x - xbar * a.sx;
+    int ybar = y0 / a.sy, oy = y0 - ybar * a.sy;  // of row y0; then a row further each time
 #pragma unroll
     for (int i = 0; i < RB; ++i) {
-        const int y = y0 + i;
-        if (y >= yend) break;
+        if (y0 + i >= yend) break;
         float m[V];
 #pragma unroll
         for (int e = 0; e < V; ++e) {
             m[e] = h[i][e];
 #pragma unroll
-            for (int t = 1; t < K; ++t) m[e] = fmaxf(m[e], h[i + t][e]);
+            for (int t = 1; t < KY; ++t) m[e] = fmaxf(m[e], h[i + t][e]);
         }
-        const int oy = y % K, ybar = y / K;
-        const size_t child = cbase + (size_t)(fy * K + oy) * Qc + (fx * K + ox);
-        // inside the child: (s - o) div K pixels per axis of a parent of s (Eqs. 6-7)
-        if (!FS_DBG_OK(a.dbg,
-                       child < (size_t)a.n_children && ybar < (hp - oy) / K - a.dbg_shrink &&
-                           xbar < (wp - ox) / K - a.dbg_shrink && ybar < a.out_h && xbar < a.out_w,
-                       DBG_POOL_WRITE))
-            continue;
+        const size_t child = cbase + (size_t)(fy * a.sy + oy) * Qc + (fx * a.sx + ox);
+        // inside the child: (n - o - k) div s + 1 pixels per axis of a parent of n (Eqs. 6-7 for s = k)
+        const bool ok = FS_DBG_OK(a.dbg,
+                                  child < (size_t)a.n_children && ybar < (hp - oy - KY) / a.sy + 1 - a.dbg_shrink &&
+                                      xbar < (wp - ox - KX) / a.sx + 1 - a.dbg_shrink && ybar < a.out_h &&
+                                      xbar < a.out_w,
+                                  DBG_POOL_WRITE);
         TO *d = out + ((child * a.out_h + ybar) * a.out_w + xbar) * a.C + cv * V;
+        if (++oy == a.sy) {
+            oy = 0;
+            ++ybar;
+        }
+        if (!ok) continue;
         if constexpr (V == 1) {
             if constexpr (BF) d[0] = f2bf(m[0]); else d[0] = m[0];
         } else {
@@ -256,40 +265,41 @@ __global__ __launch_bounds__(256) void pool_frag_rows(PoolArgs a, int nbands, in
     }
 }
 
-template <int K, int RB, bool BF, bool IN_F32, int V>
+template <int KY, int KX, int RB, bool BF, bool IN_F32, int V>
 hipError_t go_rows_rb(const PoolArgs &a, hipStream_t s)
 {
     const int nv = a.C / V;
     const int nbands = (a.in_h + RB - 1) / RB;
     const int nchunks = (a.in_w * nv + 255) / 256;
-    const long long grid = (long long)a.n_children / (K * K) * nbands * nchunks;
+    const long long grid = (long long)a.n_children / (a.sy * a.sx) * nbands * nchunks;
     const long long grid8 = (grid + 7) / 8 * 8;
     if (grid <= 0 || grid8 > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((pool_frag_rows<K, RB, BF, IN_F32, V>), dim3((unsigned)grid8), dim3(256), 0, s, a, nbands,
+    hipLaunchKernelGGL((pool_frag_rows<KY, KX, RB, BF, IN_F32, V>), dim3((unsigned)grid8), dim3(256), 0, s, a, nbands,
                        nchunks, (int)grid);
     return hipGetLastError();
 }
 
 // Filter rows per thread: the planner's choice (PoolArgs::rows).
-template <int K, bool BF, bool IN_F32, int V>
+template <int KY, int KX, bool BF, bool IN_F32, int V>
 hipError_t go_rows(const PoolArgs &a, hipStream_t s)
 {
-    if (a.rows == 4) return go_rows_rb<K, 4, BF, IN_F32, V>(a, s);
-    return go_rows_rb<K, 8, BF, IN_F32, V>(a, s);
+    if (a.rows == 4) return go_rows_rb<KY, KX, 4, BF, IN_F32, V>(a, s);
+    return go_rows_rb<KY, KX, 8, BF, IN_F32, V>(a, s);
 }
+
+// Windows with a row-band instance.
+#define FS_POOL_ROWS(X) X(2, 2) X(3, 3) X(4, 4) X(2, 3) X(3, 2)
 
 template <bool BF, bool IN_F32, int V>
 hipError_t go_k(const PoolArgs &a, int grid, hipStream_t s)
 {
-    if (a.ky == a.kx && a.sy == a.ky && a.sx == a.kx) {  // the paper's pools: stride = size
-        if (a.ky == 2) return go_rows<2, BF, IN_F32, V>(a, s);
-        if (a.ky == 3) return go_rows<3, BF, IN_F32, V>(a, s);
-        if (a.ky == 4) return go_rows<4, BF, IN_F32, V>(a, s);
-    }
+#define FS_POOL_CASE(KY, KX) \
+    if (a.ky == KY && a.kx == KX) return go_rows<KY, KX, BF, IN_F32, V>(a, s);
+    FS_POOL_ROWS(FS_POOL_CASE)
+#undef FS_POOL_CASE
     hipLaunchKernelGGL((pool_frag<BF, IN_F32, V>), dim3(grid), dim3(256), 0, s, a);
     return hipGetLastError();
 }
-
 
 }  // namespace
 
@@ -300,17 +310,21 @@ hipError_t launch_pool(const PoolArgs &a, int dtype, bool in_f32, int grid, hipS
     return (a.C % 8 == 0) ? go_k<true, false, 8>(a, grid, s) : go_k<true, false, 1>(a, grid, s);
 }
 
-std::string pool_kernel_name(int dtype, bool in_f32, int ky, int kx, int sy, int sx, int C, int rows)
+std::string pool_kernel_name(int dtype, bool in_f32, int ky, int kx, int C, int rows)
 {
     // the instance launch_pool picks, as the profiler names it
     const bool bf = dtype == DT_BF16, bin = bf && in_f32;
     const int v = !bf ? (C % 4 == 0 ? 4 : 1) : (in_f32 ? 1 : (C % 8 == 0 ? 8 : 1));
     const char *t = bf ? "true" : "false", *ti = bin ? "true" : "false";
     char buf[64];
-    if (ky == kx && sy == ky && sx == kx && ky >= 2 && ky <= 4)
-        snprintf(buf, sizeof buf, "pool_frag_rows<%d, %d, %s, %s, %d>", ky, rows == 4 ? 4 : 8, t, ti, v);
-    else
-        snprintf(buf, sizeof buf, "pool_frag<%s, %s, %d>", t, ti, v);
+#define FS_POOL_NAME(KY, KX) \
+    if (ky == KY && kx == KX) { \
+        snprintf(buf, sizeof buf, "pool_frag_rows<%d, %d, %d, %s, %s, %d>", KY, KX, rows == 4 ? 4 : 8, t, ti, v); \
+        return buf; \
+    }
+    FS_POOL_ROWS(FS_POOL_NAME)
+#undef FS_POOL_NAME
+    snprintf(buf, sizeof buf, "pool_frag<%s, %s, %d>", t, ti, v);
     return buf;
 }
 
