@@ -892,7 +892,7 @@ fs_status make_plan(const fs_net *net, int B, int H, int W, Plan &P, const View 
             L.frags = B * F * l.sy * l.sx;
             L.out_pixels = (long long)B * true_pixels(o);
             L.bytes = (double)B * in_pix * g.C * (g.is_image ? 4 : es) + (double)L.out_pixels * o.C * es;
-            L.name = pool_kernel_name(net->dtype, g.is_image, ky, kx, g.C, a.rows);
+            L.name = pool_kernel_name(net->dtype, g.is_image, ky, kx, l.sy, l.sx, g.C, a.rows);
         } else {  // conv or fc as convolution
             const int ky = l.k, kx = l.kx;
             o.Qy = g.Qy;

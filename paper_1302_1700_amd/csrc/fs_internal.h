@@ -217,7 +217,7 @@ std::string conv_direct_kernel_name(int dtype, bool in_f32, int cin, int taps);
 
 // Kernel names as the profiler reports them (for measurement reports).
 std::string conv_kernel_name(int dtype, bool in_f32, int mb, int nb, int wn, int wk, bool vec, bool hs, bool run);
-std::string pool_kernel_name(int dtype, bool in_f32, int ky, int kx, int C, int rows);
+std::string pool_kernel_name(int dtype, bool in_f32, int ky, int kx, int sy, int sx, int C, int rows);
 const char *head_kernel_name(int dtype, bool in_f32, bool has_fc);
 
 }  // namespace fs

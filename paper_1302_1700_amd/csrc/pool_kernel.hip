@@ -143,8 +143,10 @@ __global__ __launch_bounds__(256) void pool_frag(PoolArgs a)
 // pools, which the one-workgroup-per-child-row kernel above took at 1.7-2.4
 // TB/s, run at 6.4 TB/s here (95 -> 24 and 96 -> 35 us: 32 and 48 float32 channels, 3x3 / 2 and
 // 2x2 / 3 pools of 2 x 601 x 517 images).
+// sy, sx: the steps, a constant of the kernel for the paper's pools.
 template <int KY, int KX, int RB, bool BF, bool IN_F32, int V>
-__global__ __launch_bounds__(256) void pool_frag_rows(PoolArgs a, int nbands, int nchunks, int nblocks)
+__device__ __forceinline__ void pool_rows(const PoolArgs &a, const int sy, const int sx, int nbands, int nchunks,
+                                          int nblocks)
 {
     using TO = typename std::conditional<BF, uint16_t, float>::type;
     using TI = typename std::conditional<IN_F32, float, TO>::type;
@@ -170,14 +172,14 @@ __global__ __launch_bounds__(256) void pool_frag_rows(PoolArgs a, int nbands, in
     if (x > wp - KX || y0 >= yend) return;
     // the parent rows and columns the thread reads lie inside the parent's true size
     [[maybe_unused]] const int lastrow = min(y0 + RB + KY - 2, hp - 1), lastcol = x + KX - 1;
-    if (!FS_DBG_OK(a.dbg, p < a.n_children / (a.sy * a.sx) && lastrow < hp - a.dbg_shrink && lastcol < wp - a.dbg_shrink &&
+    if (!FS_DBG_OK(a.dbg, p < a.n_children / (sy * sx) && lastrow < hp - a.dbg_shrink && lastcol < wp - a.dbg_shrink &&
                               lastrow < a.in_h && lastcol < a.in_w, DBG_POOL_READ))
         return;
 
     const TI *src = reinterpret_cast<const TI *>(a.in) + (size_t)p * a.in_h * a.in_w * a.C + (size_t)x * a.C + cv * V;
     const size_t prow = (size_t)a.in_w * a.C;
-    const int Qc = a.Qx * a.sx;
-    const size_t cbase = (size_t)b * a.F * a.sy * a.sx;
+    const int Qc = a.Qx * sx;
+    const size_t cbase = (size_t)b * a.F * sy * sx;
     TO *out = reinterpret_cast<TO *>(a.out);
 
     // The RB + KY - 1 parent rows this thread reads, every load issued before
@@ -223,8 +225,8 @@ __global__ __launch_bounds__(256) void pool_frag_rows(PoolArgs a, int nbands, in
             }
         }
     }
-    const int xbar = x / a.sx, ox = x - xbar * a.sx;
-    int ybar = y0 / a.sy, oy = y0 - ybar * a.sy;  // of row y0; then a row further each time
+    const int xbar = x / sx, ox = x - xbar * sx;
+    int ybar = y0 / sy, oy = y0 - ybar * sy;  // of row y0; then a row further each time
 #pragma unroll
     for (int i = 0; i < RB; ++i) {
         if (y0 + i >= yend) break;
@@ -235,15 +237,15 @@ __global__ __launch_bounds__(256) void pool_frag_rows(PoolArgs a, int nbands, in
 #pragma unroll
             for (int t = 1; t < KY; ++t) m[e] = fmaxf(m[e], h[i + t][e]);
         }
-        const size_t child = cbase + (size_t)(fy * a.sy + oy) * Qc + (fx * a.sx + ox);
+        const size_t child = cbase + (size_t)(fy * sy + oy) * Qc + (fx * sx + ox);
         // inside the child: (n - o - k) div s + 1 pixels per axis of a parent of n (Eqs. 6-7 for s = k)
         const bool ok = FS_DBG_OK(a.dbg,
-                                  child < (size_t)a.n_children && ybar < (hp - oy - KY) / a.sy + 1 - a.dbg_shrink &&
-                                      xbar < (wp - ox - KX) / a.sx + 1 - a.dbg_shrink && ybar < a.out_h &&
+                                  child < (size_t)a.n_children && ybar < (hp - oy - KY) / sy + 1 - a.dbg_shrink &&
+                                      xbar < (wp - ox - KX) / sx + 1 - a.dbg_shrink && ybar < a.out_h &&
                                       xbar < a.out_w,
                                   DBG_POOL_WRITE);
         TO *d = out + ((child * a.out_h + ybar) * a.out_w + xbar) * a.C + cv * V;
-        if (++oy == a.sy) {
+        if (++oy == sy) {
             oy = 0;
             ++ybar;
         }
@@ -265,6 +267,18 @@ __global__ __launch_bounds__(256) void pool_frag_rows(PoolArgs a, int nbands, in
     }
 }
 
+template <int K, int RB, bool BF, bool IN_F32, int V>
+__global__ __launch_bounds__(256) void pool_frag_rows(PoolArgs a, int nbands, int nchunks, int nblocks)
+{
+    pool_rows<K, K, RB, BF, IN_F32, V>(a, K, K, nbands, nchunks, nblocks);
+}
+
+template <int KY, int KX, int RB, bool BF, bool IN_F32, int V>
+__global__ __launch_bounds__(256) void pool_frag(PoolArgs a, int nbands, int nchunks, int nblocks)
+{
+    pool_rows<KY, KX, RB, BF, IN_F32, V>(a, a.sy, a.sx, nbands, nchunks, nblocks);
+}
+
 template <int KY, int KX, int RB, bool BF, bool IN_F32, int V>
 hipError_t go_rows_rb(const PoolArgs &a, hipStream_t s)
 {
@@ -274,8 +288,10 @@ hipError_t go_rows_rb(const PoolArgs &a, hipStream_t s)
     const long long grid = (long long)a.n_children / (a.sy * a.sx) * nbands * nchunks;
     const long long grid8 = (grid + 7) / 8 * 8;
     if (grid <= 0 || grid8 > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((pool_frag_rows<KY, KX, RB, BF, IN_F32, V>), dim3((unsigned)grid8), dim3(256), 0, s, a, nbands,
-                       nchunks, (int)grid);
+    auto kern = pool_frag<KY, KX, RB, BF, IN_F32, V>;
+    if constexpr (KY == KX)
+        if (a.sy == KY && a.sx == KX) kern = pool_frag_rows<KY, RB, BF, IN_F32, V>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid8), dim3(256), 0, s, a, nbands, nchunks, (int)grid);
     return hipGetLastError();
 }
 
@@ -310,16 +326,20 @@ hipError_t launch_pool(const PoolArgs &a, int dtype, bool in_f32, int grid, hipS
     return (a.C % 8 == 0) ? go_k<true, false, 8>(a, grid, s) : go_k<true, false, 1>(a, grid, s);
 }
 
-std::string pool_kernel_name(int dtype, bool in_f32, int ky, int kx, int C, int rows)
+std::string pool_kernel_name(int dtype, bool in_f32, int ky, int kx, int sy, int sx, int C, int rows)
 {
     // the instance launch_pool picks, as the profiler names it
     const bool bf = dtype == DT_BF16, bin = bf && in_f32;
     const int v = !bf ? (C % 4 == 0 ? 4 : 1) : (in_f32 ? 1 : (C % 8 == 0 ? 8 : 1));
     const char *t = bf ? "true" : "false", *ti = bin ? "true" : "false";
     char buf[64];
+    if (ky == kx && sy == ky && sx == kx && ky >= 2 && ky <= 4) {
+        snprintf(buf, sizeof buf, "pool_frag_rows<%d, %d, %s, %s, %d>", ky, rows == 4 ? 4 : 8, t, ti, v);
+        return buf;
+    }
 #define FS_POOL_NAME(KY, KX) \
     if (ky == KY && kx == KX) { \
-        snprintf(buf, sizeof buf, "pool_frag_rows<%d, %d, %d, %s, %s, %d>", KY, KX, rows == 4 ? 4 : 8, t, ti, v); \
+        snprintf(buf, sizeof buf, "pool_frag<%d, %d, %d, %s, %s, %d>", KY, KX, rows == 4 ? 4 : 8, t, ti, v); \
         return buf; \
     }
     FS_POOL_ROWS(FS_POOL_NAME)

@@ -21,7 +21,7 @@ def fsb():
 
 
 @pytest.mark.parametrize("ky,kx", [(2, 2), (3, 3), (4, 4), (2, 3), (3, 2)])
-@pytest.mark.parametrize("sy,sx", [(1, 1), (2, 2), (3, 2), (1, 5), (5, 4)])
+@pytest.mark.parametrize("sy,sx", [(1, 1), (2, 2), (3, 2), (3, 3), (1, 5), (5, 4)])
 def test_windows_and_steps(fsb, monkeypatch, ky, kx, sy, sx):
     monkeypatch.setenv("FRAGSCAN_POOL_FUSE", "0")
     rng = np.random.default_rng(ky * 100 + kx * 10 + sy + sx)
@@ -38,7 +38,9 @@ def test_windows_and_steps(fsb, monkeypatch, ky, kx, sy, sx):
             got = net.scan(torch.from_numpy(img).cuda())
             torch.cuda.synchronize()
             net.close()
-            assert any(n.startswith("pool_frag_rows<%d, %d, %s," % (ky, kx, rows)) for n in names), names
+            name = "pool_frag_rows<%d, %s," % (ky, rows) if ky == kx == sy == sx else \
+                "pool_frag<%d, %d, %s," % (ky, kx, rows)
+            assert any(n.startswith(name) for n in names), names
             want = np.full((2, H - ky + 1, W - kx + 1, c), -np.inf, np.float32)
             for i in range(ky):
                 for j in range(kx):
