@@ -209,7 +209,8 @@ struct NetLayer {
     int nb = 1;           // output-channel blocks per wave
     int wn = 1;           // waves across output channels
     int wk = 1;           // waves splitting the K steps
-    int nbt = 0;          // channel blocks, padded to a multiple of nb * wn
+    int nbt = 0;          // channel blocks stored, at least a multiple of nb * wn
+    int mb = 0;           // pixel blocks per wave, where already chosen (0: by the tile planner)
     int ksteps = 0;
     size_t w_off = 0, b_off = 0;  // offsets into the net's device block
     // Half-step walk (c_in a multiple of 16).  bf16: vec layers whose c_in is
@@ -371,6 +372,9 @@ void pack_conv_weights(const NetLayer &l, const float *w, int dtype, std::vector
                 }
             }
 }
+
+// Whether one workgroup of the layer's tile covers all its channels.
+bool one_group(const NetLayer &l) { return l.nbt > 0 && (l.cout + 15) / 16 <= l.nb * l.wn; }
 
 // Optional tile override for tuning sweeps:
 // FRAGSCAN_TILE="L:MB,NB,WN[,BAND[,WK[,LDS]]];..." (L = layer index, LDS = least
@@ -541,6 +545,14 @@ void plan_run_tiles(const NetLayer &l, const Geo &in, int mt, int cs, int es, in
     a.lds_bytes = (int)need;
 }
 
+// LDS bytes of the partial sums a K split over wk waves exchanges: every wave
+// hands the blocks it does not finish to their owners.
+size_t split_k_lds(int mb, int nb, int wk)
+{
+    const int me = (mb + wk - 1) / wk;
+    return (size_t)wk * (wk - 1) * (4 / wk) * me * nb * 64 * 16;
+}
+
 // Tile choice for a conv launch (the tiling itself is described in conv_impl.h).
 // wide: the float32 4 x 13 tile of conv_f32_wide.hip (l.nb = 13, l.wn = 1),
 // which has no entry in the shared tile lists.
@@ -576,6 +588,7 @@ fs_status plan_conv_tiles(const fs_net *net, const NetLayer &l, const Geo &in, L
     // K walks of workload 3's 2x2x16 -> 100 layer, 742 -> 688 us against two,
     // and workload 5's gathered 3x3x3 -> 32 first layer), else the neighbours
     const int mbs[4] = {4, 2, 1, 8};
+    if (!mb_force) mb_force = l.mb;
     for (int mi = 0; mi < 4; ++mi) {
         const int mb = mb_force ? mb_force : mbs[mi];
         if (wide ? mb != 4 : !conv_tile_supported(mb, l.nb, l.wn, l.wk, l.vec, l.hs)) {
@@ -594,7 +607,7 @@ fs_status plan_conv_tiles(const fs_net *net, const NetLayer &l, const Geo &in, L
             if ((long long)hout_max * band_w >= (1 << 20)) continue;
             const size_t red = (size_t)l.wn * mt * kMaxFusedClasses * 4;  // fused-head reduction
             // split-K partial sums of the waves with wk > 0
-            const size_t part = (size_t)(l.wk - 1) * (4 / l.wk) * mb * l.nb * 4 * 64 * 4;
+            const size_t part = split_k_lds(mb, l.nb, l.wk);
             // Stores: straight from the registers (16-byte runs of 4 f32 or
             // 8 bf16 channels per lane; measured no slower than restaging on
             // every conv layer of the five workloads, faster on the bf16 and
@@ -723,6 +736,7 @@ fs_status plan_conv_pool_tiles(const fs_net *net, const NetLayer &l, const Geo &
     int mb_force = 0, band_force = 0;
     tile_override(L.layer, &mb_force, nullptr, nullptr, &band_force);
     const int mbs[4] = {4, 8, 2, 1};
+    if (!mb_force) mb_force = l.mb;
     for (int mi = 0; mi < 4; ++mi) {
         const int mb = mb_force ? mb_force : mbs[mi];
         if (!conv_tile_supported(mb, l.nb, l.wn, l.wk, l.vec, l.hs)) {
@@ -733,6 +747,20 @@ fs_status plan_conv_pool_tiles(const fs_net *net, const NetLayer &l, const Geo &
         const int wmax = std::max(wM_max, 1), hmax = std::max(hM_max, 1);
         int nbands = wmax <= 32 ? 1 : (wmax + 15) / 16;
         if (band_force) nbands = (wmax + band_force - 1) / band_force;
+        if (l.mb && !band_force) {
+            // a small grid's tile of few pixels: the bands that need the
+            // fewest tiles
+            long long best = 1LL << 40;
+            for (int n = 1; n <= wmax; ++n) {
+                const int bw = (wmax + n - 1) / n, rt = std::min(mt / (bw + kpx - 1) - (kpy - 1), hmax);
+                if (rt < 1) continue;
+                const long long tiles = (long long)n * ((hmax + rt - 1) / rt);
+                if (tiles < best) {
+                    best = tiles;
+                    nbands = n;
+                }
+            }
+        }
         for (; nbands <= wmax; ++nbands) {
             const int band_w = (wmax + nbands - 1) / nbands;
             const int ew = band_w + kpx - 1;
@@ -740,7 +768,7 @@ fs_status plan_conv_pool_tiles(const fs_net *net, const NetLayer &l, const Geo &
             if (rt < 1) continue;  // narrower bands
             const size_t win = offtab + (size_t)(rt + kpy - 1 + ky - 1) * (ew + kx - 1) * cs * es;
             const size_t tile = (size_t)mt * (l.wn * l.nb * 16 + tpad) * es;
-            const size_t part = (size_t)(l.wk - 1) * (4 / l.wk) * mb * l.nb * 4 * 64 * 4;
+            const size_t part = split_k_lds(mb, l.nb, l.wk);
             const size_t need = std::max(std::max(win, tile), part);
             if (win > 96 * 1024 || need > kMaxLdsBytes) {
                 if (band_w <= 8) break;
@@ -763,6 +791,56 @@ fs_status plan_conv_pool_tiles(const fs_net *net, const NetLayer &l, const Geo &
     return fail(FS_ERR_UNSUPPORTED, "layer %d: no fused convolution + pool tile", L.layer);
 }
 
+// Tiles of mt output pixels a layer's fragments need (counted up to limit).
+long long count_tiles(const Geo &in, int ky, int kx, int B, int mt, long long limit)
+{
+    long long n = 0;
+    for (int hy : in.ey)
+        for (int wx : in.ex) {
+            const long long px = (long long)std::max(hy - ky + 1, 0) * std::max(wx - kx + 1, 0);
+            n += (px + mt - 1) / mt * B;
+            if (n > limit) return n;
+        }
+    return n;
+}
+
+// Register tile of a split float32 layer on a grid that does not fill the
+// device: the fewest pixels per workgroup that still leave it few enough
+// workgroups per CU, since there a launch takes as long as one workgroup's
+// walk over K.  48 -> 48 layers (3 blocks, split K) go from 128 pixels and two
+// K parts to 64 or 32 pixels and four; FC layers of 129-224 outputs (7 x 2)
+// to 16 or 32 pixels (four waves across the channels).  Measured on N4, us per launch, 128 / 64 / 32 pixels
+// (the grid of 64-pixel tiles in workgroups): 5x5 on 103x110 (~170) 14.5 /
+// 10.8 / 11.0, on 128^2 (240) 15.0 / 11.4 / 11.9, on 180^2 (430) 16.5 / 15.2 /
+// 20.1, on 256^2 (915) 24.5 / 25.5 / 34.0; last 4x4 on 128^2 (64; 128 of 32
+// pixels) 11.0 / 8.5 / 7.7, on 256^2 (640) 18.4 / 15.9 / 22.3.  FC1 + head, 128
+// / 32 / 16 pixels: 128^2 (256 fragments of 4-9 pixels) 20.6 / 11.0 / 10.2, 180^2
+// (25-36) 20.9 / 14.4 / 23.1, 256^2 (100-121) 21.4 / 28.6 / 45.9.
+void small_grid_tile(const fs_net *net, int li, const Geo &in, int B, NetLayer &l)
+{
+    if (!l.hs || net->dtype != DT_F32 || tile_override(li, nullptr, nullptr, nullptr, nullptr)) return;
+    if (const char *e = getenv("FRAGSCAN_RUN"); e && e[0]) return;  // run tiles forced on or off: the layer's own tile
+    const int ncu = net->ncu > 0 ? net->ncu : 256;
+    struct Shape { int mb, nb, wn, wk, quarters; };  // at most quarters / 4 workgroups per CU
+    static const Shape narrow[] = {{2, 3, 1, 4, 3}, {4, 3, 1, 4, 10}};
+    static const Shape wide[] = {{1, 4, 4, 1, 8}, {2, 4, 4, 1, 8}};
+    const Shape *s = nullptr;
+    int n = 0;
+    if (l.nb == 3 && l.wn == 1 && l.wk == 2 && l.ksteps_h >= 4)
+        s = narrow, n = 2;
+    else if (l.nb == 7 && l.wn == 2 && l.wk == 1 && one_group(l) && !getenv("FRAGSCAN_WIDE"))
+        s = wide, n = 2;
+    for (int i = 0; i < n; ++i) {
+        const long long most = (long long)ncu * s[i].quarters / 4;
+        if (count_tiles(in, l.k, l.kx, B, 16 * s[i].mb * 4 / (s[i].wn * s[i].wk), most) > most) continue;
+        l.mb = s[i].mb;
+        l.nb = s[i].nb;
+        l.wn = s[i].wn;
+        l.wk = s[i].wk;
+        return;
+    }
+}
+
 // Whether the pool after conv layer li goes into the convolution's epilogue.
 // Per output pixel, fusing recomputes a halo share `ov` of the products
 // (2 c_in k^2 c_out ov FLOPs; ov ~ 0.35 for 2 x 2 pools with 16-column
@@ -771,14 +849,18 @@ fs_status plan_conv_pool_tiles(const fs_net *net, const NetLayer &l, const Geo &
 // c_in k^2 ov < elem * (peak FLOP/s / HBM bytes/s): every layer of the five
 // workloads except N4's 48 -> 48 convolutions, whose fused form measured
 // 10-35% slower.  FRAGSCAN_POOL_FUSE=1 / 0 forces it on / off.
-bool want_pool_fusion(const fs_net *net, int li)
+// small: the layer's grid of 64-pixel tiles is at most one workgroup per CU;
+// the separate pool's launch costs more there than the recomputed halo (N4 on
+// 103x110: 60 -> 54 us a scan, 128^2 66 -> 62; 180^2, 430 workgroups, the same).
+bool want_pool_fusion(const fs_net *net, int li, const NetLayer &l, bool small)
 {
     const int nl = (int)net->L.size();
     if (li + 1 >= nl) return false;
-    const NetLayer &l = net->L[li], &p = net->L[li + 1];
-    if (l.kind == FS_MAXPOOL || p.kind != FS_MAXPOOL || l.nbt != l.nb * l.wn) return false;
+    const NetLayer &p = net->L[li + 1];
+    if (l.kind == FS_MAXPOOL || p.kind != FS_MAXPOOL || !one_group(l)) return false;
     if (p.sy != p.k || p.sx != p.kx) return false;  // the fused walk samples the filter at steps of k
     if (const char *e = getenv("FRAGSCAN_POOL_FUSE"); e && e[0]) return e[0] == '1';
+    if (small) return true;
     const double ov = (p.k == 2 && p.kx == 2) ? 0.35 : 0.5;
     const double ridge = net->dtype == DT_BF16 ? 2516.6e12 / 8e12 : 157.3e12 / 8e12;  // FLOP per byte
     return (double)l.cin * l.k * l.kx * ov < elem_of(net->dtype) * ridge;
@@ -841,7 +923,7 @@ fs_status make_plan(const fs_net *net, int B, int H, int W, Plan &P, const View 
     bool fuse = false;
     if (net->head_fc && net->ncls <= kMaxFusedClasses && nl >= 2) {
         const NetLayer &pl = net->L[nl - 2];
-        fuse = pl.kind != FS_MAXPOOL && pl.nbt == pl.nb * pl.wn && !getenv("FRAGSCAN_NO_FUSED_HEAD");
+        fuse = pl.kind != FS_MAXPOOL && one_group(pl) && !getenv("FRAGSCAN_NO_FUSED_HEAD");
     }
     int cur = -1;  // where the current activations live
     size_t buf = 0;
@@ -921,6 +1003,10 @@ fs_status make_plan(const fs_net *net, int B, int H, int W, Plan &P, const View 
                 l.hs = any && l.ksteps_h >= l.wk && !(sp && sp[0] == '0');
                 if (l.hs) l.ksteps = l.ksteps_h;
             }
+            small_grid_tile(net, li, g, B, l);
+            const bool small = l.mb > 0 && l.wk == 4 &&
+                               count_tiles(g, ky, kx, B, 64, net->ncu > 0 ? net->ncu : 256) <=
+                                   (net->ncu > 0 ? net->ncu : 256);
             L.vec = l.vec;
             L.hs = l.hs;
             L.nb = l.nb;
@@ -954,7 +1040,8 @@ fs_status make_plan(const fs_net *net, int B, int H, int W, Plan &P, const View 
             // it for every layer it supports, =0 for none.
             const char *dv = getenv("FRAGSCAN_DIRECT");
             const bool want_direct = dv ? dv[0] == '1' : l.cout <= 16;
-            const bool pool_fuse = !fused_here && want_pool_fusion(net, li);
+            const bool pool_fuse = !fused_here && want_pool_fusion(net, li, l, small);
+            if (pool_fuse && small) l.mb = 4;  // 64 pixels: room for the halo
             if (l.has_w32 && !fused_here && !pool_fuse && want_direct) {
                 L.direct = true;
                 L.conv.lds_bytes = 0;
@@ -978,7 +1065,7 @@ fs_status make_plan(const fs_net *net, int B, int H, int W, Plan &P, const View 
                 // grids, where the 7 x 2 tiles run two per CU, 14% slower).
                 // FRAGSCAN_WIDE=1 / 0 forces it on / off where it applies.
                 if (fused_here && !pool_fuse && net->dtype == DT_F32 && l.vec && l.nb == 7 && l.wn == 2 &&
-                    l.wk == 1 && l.nbt == 14 && l.cout <= 13 * 16) {
+                    l.wk == 1 && one_group(l) && l.cout <= 13 * 16) {
                     const long long tiles = (long long)B * F * a.nbands * (a.run ? L.frag_tiles : a.tiles_per_band);
                     bool wide = net->ncu > 0 && !l.hs && tiles <= 12LL * net->ncu &&
                                 conv_blocks_per_cu(net->dtype, g.is_image, L.mb, l.nb, l.wn, l.wk, l.vec, false, false,
@@ -1089,7 +1176,7 @@ fs_status make_plan(const fs_net *net, int B, int H, int W, Plan &P, const View 
                 // second half ends in padding (ConvArgs::swapn);
                 // FRAGSCAN_SWAP=0 keeps them in place.
                 const char *sw = getenv("FRAGSCAN_SWAP");
-                a.swapn = a.nbu < a.nbt && !(sw && sw[0] == '0');
+                a.swapn = a.nbu < L.nb * L.wn && !(sw && sw[0] == '0');
                 L.dst = 2;
                 L.n_layers = 2;
                 const long long npix = (long long)B * P.ny * P.nx;
@@ -1653,6 +1740,9 @@ static fs_status net_create(const fs_layer *layers, int32_t n_layers, int32_t in
         }
         const int grp = l.nb * l.wn;
         l.nbt = (nbt0 + grp - 1) / grp * grp;
+        // (16 blocks, so that small grids can take the same weights with four
+        // waves of four across the channels)
+        if (dtype == FS_F32 && l.vec && l.nb == 7 && l.wn == 2 && l.nbt == 14) l.nbt = 16;
         l.ksteps = (l.k * l.kx * l.cin + KSTEP - 1) / KSTEP;
         if (l.ksteps < l.wk) {  // every K-splitting wave needs at least one step
             delete net;

@@ -184,7 +184,7 @@ __device__ __forceinline__ bool head_two_class(const ConvArgs &a)
 }
 
 template <int MB, int NB, int WN, bool BF>
-__device__ __forceinline__ void fused_head_partials(const ConvArgs &a, const f4 (&acc)[MB][NB], int nb0, int wm,
+__device__ __forceinline__ void fused_head_partials(const ConvArgs &a, const f4 (&acc)[MB][NB], int nb0, int mb0,
                                                     int wn, int lm, int g, float *red)
 {
     constexpr int NC = kMaxFusedClasses;
@@ -291,7 +291,7 @@ __device__ __forceinline__ void fused_head_partials(const ConvArgs &a, const f4 
     if (g == 0) {
 #pragma unroll
         for (int i = 0; i < MB; ++i) {
-            const int m = (wm * MB + i) * 16 + lm;
+            const int m = (mb0 + i) * 16 + lm;
 #pragma unroll
             for (int c = 0; c < NC; ++c) red[((size_t)wn * a.mt + m) * NC + c] = part[i][c];
         }
@@ -382,6 +382,16 @@ constexpr int min_blocks(int mb, int nb, bool bf, bool hs)
 {
     if (!bf && nb == 1 && mb <= 4) return hs ? 4 : 6;
     return hs && mb * nb >= 24 ? 2 : 1;
+}
+
+// Weight register sets of the half-step walk: enough steps ahead that their
+// products (16 cycles each) cover the ~1000 cycles of a load, where registers
+// are not what limits the waves per SIMD.
+constexpr int half_step_ring(int mb, int nb, bool bf)
+{
+    const int cycles = mb * nb * 16 * (bf ? 1 : 3);
+    if (mb * nb >= 12) return 1;
+    return cycles >= 384 || (mb == 4 && nb == 1) ? 2 : 4;
 }
 
 template <int MB, int NB, int WN, int WK, bool BF, bool IN_F32, bool VEC, bool RUN, bool HS>
@@ -802,35 +812,40 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
             constexpr int NBA = decltype(nbac)::value;
             const int nh = a.cin / 16, nhs = a.ky * a.kx * nh;
             const int s_begin = (a.ksteps * wk) / WK, nsteps = (a.ksteps * (wk + 1)) / WK - s_begin;
+            // half step hs at tap column dx, channel group cc, window offset
+            // pos; both halves of a step's offsets, one per lane
             int hs = 2 * s_begin;
-            int cc = hs % nh, dx = (hs / nh) % a.kx, dy = (hs / nh) / a.kx;
+            int cc = hs % nh, dx = (hs / nh) % a.kx;
+            int pos = ((hs / nh) / a.kx * Cc + dx) * CS + cc * 16;
+            const int tap_skip = CS - a.cin, row_skip = (Cc - a.kx) * CS;
             const bool upper = g >= 2;
-            auto pos = [&] { return (dy * Cc + dx) * CS + cc * 16; };
-            auto advance = [&] {  // the next half step (stays at the last one)
-                const int more = hs + 1 < nhs;
-                hs += more;
-                cc += more;
-                const int w1 = cc == nh;
+            auto advance = [&] {
+                ++hs;
+                ++cc;
+                pos += 16;
+                const bool w1 = cc == nh;
                 cc = w1 ? 0 : cc;
+                pos += w1 ? tap_skip : 0;
                 dx += w1;
-                const int w2 = dx == a.kx;
+                const bool w2 = dx == a.kx;
                 dx = w2 ? 0 : dx;
-                dy += w2;
+                pos += w2 ? row_skip : 0;
             };
             auto step_off = [&] {
-                const int lo = pos();
+                const int lo = pos;
                 advance();
-                const int hi = pos();
+                const int hi = hs < nhs ? pos : lo;  // past an odd end: the last group again
                 advance();
                 return upper ? hi : lo;
             };
             constexpr int PX = MB * NB >= 24 ? 1 : 2;  // pixel register sets (one: reloaded after the step's products)
-            u4 b[NB][NW], av[PX][MB][NW];
+            constexpr int WD = half_step_ring(MB, NB, BF);   // weight register sets: steps they are loaded ahead
+            u4 b[WD][NB][NW], av[PX][MB][NW];
             const size_t wstep_h = (size_t)a.nbt * 64 * NW;
             const u4 *wnx = reinterpret_cast<const u4 *>(a.w) + (size_t)nb0 * 64 * NW + lane + (size_t)s_begin * wstep_h;
-            auto load_w = [&](const u4 *src, int j) {
+            auto load_w = [&](u4(&w)[NB][NW], const u4 *src, int j) {
 #pragma unroll
-                for (int p = 0; p < NW; ++p) b[j][p] = src[(j * NW + p) * 64];
+                for (int p = 0; p < NW; ++p) w[j][p] = src[(j * NW + p) * 64];
             };
             auto load_px = [&](u4(&v)[MB][NW], int off) {
 #pragma unroll
@@ -838,16 +853,24 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
 #pragma unroll
                     for (int p = 0; p < NW; ++p) v[i][p] = *reinterpret_cast<const u4 *>(win_lds + abase[i] + off + p * LPE);
             };
+            const int last = nsteps - 1;
 #pragma unroll
-            for (int j = 0; j < NBA; ++j) load_w(wnx, j);
+            for (int t = 0; t < WD; ++t) {
+#pragma unroll
+                for (int j = 0; j < NBA; ++j) load_w(b[t], wnx, j);
+                wnx += t < last ? wstep_h : 0;  // (past the last step: the last again, unused)
+            }
             const int off0 = step_off();
             load_px(av[0], off0);
-            auto step = [&](int s, const u4(&x)[MB][NW], u4(&xn)[MB][NW]) {
-                const bool more = s + 1 < nsteps;
-                const int off = step_off();
-                if constexpr (PX == 2) load_px(xn, more ? off : off0);
-                wnx += more ? wstep_h : 0;
+            int off = step_off();  // of the next step
+            // one step: pixels x and weights w, reloaded for step s + WD
+            auto step = [&](int s, const u4(&x)[MB][NW], u4(&xn)[MB][NW], u4(&w)[NB][NW]) {
+                const int offn = s < last ? off : off0;
+                if constexpr (PX == 2) load_px(xn, offn);
                 __builtin_amdgcn_sched_barrier(0);
+                // the next step's offset, in scalar instructions that issue
+                // between the first block's products
+                off = step_off();
 #pragma unroll
                 for (int j = 0; j < NBA; ++j) {
                     if constexpr (SPLIT) {
@@ -856,28 +879,45 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
 #pragma unroll
                             for (int i = 0; i < MB; ++i)
                                 acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                                    __builtin_bit_cast(h8v, b[j][p == 2]), __builtin_bit_cast(h8v, x[i][p == 1]),
+                                    __builtin_bit_cast(h8v, w[j][p == 2]), __builtin_bit_cast(h8v, x[i][p == 1]),
                                     acc[i][j], 0, 0, 0);
                     } else {
 #pragma unroll
                         for (int i = 0; i < MB; ++i)
                             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                __builtin_bit_cast(bf8, b[j][0]), __builtin_bit_cast(bf8, x[i][0]), acc[i][j], 0, 0, 0);
+                                __builtin_bit_cast(bf8, w[j][0]), __builtin_bit_cast(bf8, x[i][0]), acc[i][j], 0, 0, 0);
                     }
-                    load_w(wnx, j);
+                    if (j == 0) {
+#pragma unroll
+                        for (int k = 0; k < MB * (SPLIT ? 3 : 1); ++k) {
+                            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one product
+                            __builtin_amdgcn_sched_group_barrier(0x006, 3, 0);  // up to three scalar / vector instructions
+                        }
+                    }
                     __builtin_amdgcn_sched_barrier(0);
+                    load_w(w, wnx, j);
                 }
+                __builtin_amdgcn_sched_barrier(0);
                 if constexpr (PX == 1) {
-                    load_px(xn, more ? off : off0);
+                    load_px(xn, offn);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             };
+            constexpr int U = WD > PX ? WD : PX;
             int s = 0;
-            for (; s + 2 <= nsteps; s += 2) {
-                step(s, av[0], av[PX - 1]);
-                step(s + 1, av[PX - 1], av[0]);
+            for (; s + U <= nsteps; s += U) {
+#pragma unroll
+                for (int t = 0; t < U; ++t) {
+                    step(s + t, av[t % PX], av[(t + 1) % PX], b[t % WD]);
+                    wnx += s + t + WD < last ? wstep_h : 0;
+                }
             }
-            if (s < nsteps) step(s, av[0], av[PX - 1]);
+#pragma unroll
+            for (int t = 0; t + 1 < U; ++t)
+                if (s + t < nsteps) {
+                    step(s + t, av[t % PX], av[(t + 1) % PX], b[t % WD]);
+                    wnx += s + t + WD < last ? wstep_h : 0;
+                }
         };
         if constexpr (WN == 2 && WK == 1 && NB >= 2) {
             if (nb0 + NB - 1 >= a.nbu)
@@ -886,15 +926,6 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
                 kwalk(std::integral_constant<int, NB>());
         } else {
             kwalk(std::integral_constant<int, NB>());
-        }
-        if constexpr (SPLIT) {
-            // back from the operands' power-of-two scales (exact)
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                const f4 us = *reinterpret_cast<const f4 *>(a.unscale + (nb0 + j) * 16 + 4 * g);
-#pragma unroll
-                for (int i = 0; i < MB; ++i) acc[i][j] *= us;
-            }
         }
     } else if constexpr (VEC) {
         auto kwalk = [&](auto nbac) {
@@ -1056,39 +1087,65 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
     }
 
     // ---- split-K reduction ----------------------------------------------------
+    // The waves of a K split share the finish: wave wk adds up and owns pixel
+    // blocks wk*ME .. of the wave tile (with fewer blocks than waves the last
+    // waves own none), each partial sum read once from LDS, summed in the
+    // order of the K parts.
+    constexpr int ME = (MB + WK - 1) / WK;  // pixel blocks a wave finishes
+    const int mb0 = wm * MB + wk * ME;      // ... from block mb0 of the tile on
+    const bool own = wk * ME < MB;
+    f4 fin[WK > 1 ? ME : 1][WK > 1 ? NB : 1];
+    f4(&eacc)[ME][NB] = [&]() -> f4(&)[ME][NB] {
+        if constexpr (WK > 1) return fin; else return acc;
+    }();
     if constexpr (WK > 1) {
-        constexpr int RV = MB * NB * 4;  // accumulator floats per lane
-        float *part = reinterpret_cast<float *>(smem);
+        // slot (owner d, source s != d, wave column wmn, block): 64 lanes x 16 bytes
+        f4 *part = reinterpret_cast<f4 *>(smem);
+        auto slot = [&](int d, int src, int i, int j) {
+            return part + (size_t)((((d * (WK - 1) + src - (src > d)) * WMN + wmn) * ME + i) * NB + j) * 64 + lane;
+        };
         __syncthreads();  // the window is no longer read
-        if (wk > 0) {
-            float *dst = part + ((size_t)((wk - 1) * WMN + wmn) * RV) * 64 + lane;
 #pragma unroll
-            for (int i = 0; i < MB; ++i)
+        for (int d = 0; d < WK; ++d)
+            if (d != wk && d * ME < MB) {
 #pragma unroll
-                for (int j = 0; j < NB; ++j)
+                for (int i = 0; i < ME; ++i)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) dst[(size_t)((i * NB + j) * 4 + e) * 64] = acc[i][j][e];
-        }
-        __syncthreads();
-        if (wk == 0) {
-#pragma unroll
-            for (int w = 1; w < WK; ++w) {
-                const float *src = part + ((size_t)((w - 1) * WMN + wmn) * RV) * 64 + lane;
-#pragma unroll
-                for (int i = 0; i < MB; ++i)
-#pragma unroll
-                    for (int j = 0; j < NB; ++j)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) acc[i][j][e] += src[(size_t)((i * NB + j) * 4 + e) * 64];
+                    for (int j = 0; j < NB; ++j) *slot(d, wk, i, j) = acc[(d * ME + i) % MB][j];
             }
+        __syncthreads();
+#pragma unroll
+        for (int d = 0; d < WK; ++d)
+            if (d == wk && d * ME < MB) {
+#pragma unroll
+                for (int i = 0; i < ME; ++i)
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) {
+                        f4 t = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int w = 0; w < WK; ++w) {
+                            const f4 v = w == d ? acc[(d * ME + i) % MB][j] : *slot(d, w, i, j);
+                            t = w == 0 ? v : t + v;
+                        }
+                        fin[i][j] = t;
+                    }
+            }
+    }
+    if constexpr (SPLIT) {
+        // back from the operands' power-of-two scales (exact)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            const f4 us = *reinterpret_cast<const f4 *>(a.unscale + (nb0 + j) * 16 + 4 * g);
+#pragma unroll
+            for (int i = 0; i < ME; ++i) eacc[i][j] *= us;
         }
     }
 
-    // ---- epilogue (only the wk == 0 waves hold the sums) ----------------------
+    // ---- epilogue (each wave over the blocks it finishes) ---------------------
     if (a.head_ncls > 0) {
         float *red = reinterpret_cast<float *>(smem);
         __syncthreads();  // the LDS window / partial sums (which red reuses) are no longer read
-        if (wk == 0) fused_head_partials<MB, NB, WN, BF>(a, acc, nb0, wm, wn, lm, g, red);
+        if (own) fused_head_partials<ME, NB, WN, BF>(a, eacc, nb0, mb0, wn, lm, g, red);
         __syncthreads();
         fused_head_finish<WN>(
             a, q / a.F, npix,
@@ -1108,7 +1165,20 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
     // bytes per block.  Channels past c_out (padding blocks) and pixels past
     // the tile are not written.
     const bool act_tanh = a.act == ACT_TANH;
-    auto act = [&](float v) { return act_tanh ? tanh_fast(v) : v; };
+    // (half-step tiles whose waves split K: in place, under one uniform branch; in
+    // the others it costs registers, and with them a wave per SIMD)
+    constexpr bool IN_PLACE = HS && WK > 1 && ME * NB <= 16;
+    if constexpr (IN_PLACE) {
+        if (act_tanh) {
+#pragma unroll
+            for (int i = 0; i < ME; ++i)
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) eacc[i][j][e] = tanh_fast(eacc[i][j][e]);
+        }
+    }
+    auto act = [&](float v) { return !IN_PLACE && act_tanh ? tanh_fast(v) : v; };
     constexpr bool PAIRED = BF && (NB % 2) == 0;
     constexpr int CRUN = PAIRED ? 8 : 4;  // consecutive channels per lane and block (pair)
 
@@ -1119,10 +1189,10 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
     constexpr int TS = NW + TPAD;
     // keys: bf16 runs are written as order keys (bf16x2_key), for the pool
     auto stage_tile = [&](TC *tile, bool keys) {
-        if (wk != 0) return;
+        if (!own) return;
 #pragma unroll
-        for (int i = 0; i < MB; ++i) {
-            TC *row = tile + ((wm * MB + i) * 16 + lm) * TS;
+        for (int i = 0; i < ME; ++i) {
+            TC *row = tile + ((mb0 + i) * 16 + lm) * TS;
             if constexpr (PAIRED) {
 #pragma unroll
                 for (int p = 0; p < NB / 2; ++p) {
@@ -1130,8 +1200,8 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
                     float h[8];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        h[e] = act(acc[i][2 * p][e]);
-                        h[4 + e] = act(acc[i][2 * p + 1][e]);
+                        h[e] = act(eacc[i][2 * p][e]);
+                        h[4 + e] = act(eacc[i][2 * p + 1][e]);
                     }
                     u4 pk;
 #pragma unroll
@@ -1147,16 +1217,16 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
                     TC *dst = row + (wn * NB + j) * 16 + 4 * g;
                     if constexpr (BF) {
                         uint2 pk;
-                        pk.x = pack_bf16(act(acc[i][j][0]), act(acc[i][j][1]));
-                        pk.y = pack_bf16(act(acc[i][j][2]), act(acc[i][j][3]));
+                        pk.x = pack_bf16(act(eacc[i][j][0]), act(eacc[i][j][1]));
+                        pk.y = pack_bf16(act(eacc[i][j][2]), act(eacc[i][j][3]));
                         if (keys) {
                             pk.x = bf16x2_key(pk.x);
                             pk.y = bf16x2_key(pk.y);
                         }
                         *reinterpret_cast<uint2 *>(dst) = pk;
                     } else {
-                        *reinterpret_cast<f4 *>(dst) = f4{act(acc[i][j][0]), act(acc[i][j][1]), act(acc[i][j][2]),
-                                                          act(acc[i][j][3])};
+                        *reinterpret_cast<f4 *>(dst) = f4{act(eacc[i][j][0]), act(eacc[i][j][1]), act(eacc[i][j][2]),
+                                                          act(eacc[i][j][3])};
                     }
                 }
             }
@@ -1362,15 +1432,15 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
     }
 
     // Direct: every lane writes its runs straight from registers.
-    if (wk != 0) return;
+    if (!own) return;
     const size_t osz = (size_t)a.out_h * a.out_w * a.cout;
     TC *outp = reinterpret_cast<TC *>(a.out) + (size_t)q * osz;
     TC *outp1 = reinterpret_cast<TC *>(a.out) + (size_t)q1 * osz;
     const int orow = a.out_w * a.cout;
     const bool full = (a.cout % CRUN) == 0;
 #pragma unroll
-    for (int i = 0; i < MB; ++i) {
-        const int m = (wm * MB + i) * 16 + lm;
+    for (int i = 0; i < ME; ++i) {
+        const int m = (mb0 + i) * 16 + lm;
         if (m >= npix) continue;
         int seg, y, x;
         locate(m, seg, y, x);
@@ -1385,8 +1455,8 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
                 float h[8];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    h[e] = act(acc[i][2 * p][e]);
-                    h[4 + e] = act(acc[i][2 * p + 1][e]);
+                    h[e] = act(eacc[i][2 * p][e]);
+                    h[4 + e] = act(eacc[i][2 * p + 1][e]);
                 }
                 u4 pk;
 #pragma unroll
@@ -1406,7 +1476,7 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
                 if (ch >= a.cout) continue;
                 float v[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = act(acc[i][j][e]);
+                for (int e = 0; e < 4; ++e) v[e] = act(eacc[i][j][e]);
                 if constexpr (BF) {
                     uint2 pk;
                     pk.x = pack_bf16(v[0], v[1]);
@@ -1482,8 +1552,9 @@ hipError_t launch_one(const ConvArgs &a, int gx, int gy, hipStream_t s)
 #define FS_CONV_TILES_HS(X)                                                                     \
     X(1, 1, 1, 1) X(1, 2, 1, 1) X(1, 3, 1, 1) X(1, 4, 1, 1) X(2, 1, 1, 1) X(2, 2, 1, 1)          \
     X(2, 3, 1, 1) X(2, 4, 1, 1) X(4, 1, 1, 1) X(4, 2, 1, 1) X(4, 3, 1, 1) X(4, 4, 1, 1)          \
-    X(8, 3, 1, 1) X(2, 7, 1, 1) X(4, 7, 1, 1) X(2, 7, 2, 1) X(4, 7, 2, 1) X(4, 4, 2, 1)          \
-    X(2, 4, 4, 1) X(4, 4, 4, 1) X(2, 3, 1, 2) X(4, 3, 1, 2) X(8, 3, 1, 2) X(8, 3, 1, 4)
+    X(2, 7, 1, 1) X(4, 7, 1, 1) X(2, 7, 2, 1) X(4, 7, 2, 1) X(4, 4, 2, 1)          \
+    X(1, 4, 4, 1) X(2, 4, 4, 1) X(4, 4, 4, 1) X(2, 3, 1, 2) X(4, 3, 1, 2)                          \
+    X(1, 3, 1, 4) X(2, 3, 1, 4) X(4, 3, 1, 4)
 #define FS_CONV_TILES_RUN_HS(X) \
     X(2, 2, 1, 1) X(4, 2, 1, 1) X(4, 3, 1, 1) X(4, 3, 1, 2) X(4, 4, 1, 1) X(4, 7, 1, 1) X(4, 7, 2, 1)
 

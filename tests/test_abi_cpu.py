@@ -717,3 +717,30 @@ def test_half_step_layers(monkeypatch):
     assert off[0] == set() and off[1:] == on[1:]
     monkeypatch.setenv("FRAGSCAN_SPLIT", "1")
     assert half(scores, "f32")[0] == {2, 4, 6, 8}
+
+
+def test_small_grid_tiles(monkeypatch):
+    """Split float32 layers whose grid leaves the device part empty take tiles
+    of fewer pixels (plan-only nets count 256 CUs), and the smallest grids
+    fuse the pools too; larger ones and forced tiles keep the 128-pixel
+    tiles.  Work and map are the same."""
+    for v in ("FRAGSCAN_TILE", "FRAGSCAN_RUN", "FRAGSCAN_POOL_FUSE"):
+        monkeypatch.delenv(v, raising=False)
+    net = _plan_net(wl.n4_layers())
+    tile = lambda H: {L["layer"]: L["name"].split("<")[1].split(", false")[0] + ("+pool" if "+pool" in L["name"] else "")
+                      for L in net.launches(1, H, H) if L["kind"] == 0}
+    assert tile(128) == {0: "4, 3, 1, 1+pool", 2: "4, 3, 1, 4+pool", 4: "4, 3, 1, 4+pool", 6: "4, 3, 1, 4+pool",
+                         8: "1, 4, 4, 1"}
+    mid = tile(180)
+    assert (mid[2], mid[4], mid[8]) == ("4, 3, 1, 4", "4, 3, 1, 4", "2, 4, 4, 1")
+    big = tile(512)
+    assert {big[i] for i in (2, 4, 6)} == {"4, 3, 1, 2"} and big[8] == "4, 7, 2, 1"
+    assert net.plan(1, 128, 128)["n_launches"] == 5 and net.plan(1, 512, 512)["n_launches"] == 8
+    flops = net.plan(1, 128, 128)["flops"]
+    monkeypatch.setenv("FRAGSCAN_SPLIT", "0")
+    assert net.plan(1, 128, 128)["flops"] == flops
+    monkeypatch.delenv("FRAGSCAN_SPLIT")
+    monkeypatch.setenv("FRAGSCAN_TILE", "2:4,3,1,0,2;4:4,3,1,0,2;6:4,3,1,0,2;8:4,7,2")
+    forced = tile(128)
+    assert forced[2] == "4, 3, 1, 2" and forced[8] == "4, 7, 2, 1"
+    net.close()

@@ -97,6 +97,8 @@ def test_same_values_on_every_tile_path(fsb, monkeypatch, env, dt):
     w0 = ix.patch_size(layers)
     params = wl.make_weights(layers, 9, 0.08)
     img = wl.make_image(10, 2, w0 + 121, w0 + 108, 1)
+    if "FRAGSCAN_RUN" in env:  # (a small grid takes another split of K unless run tiles are forced off or on)
+        monkeypatch.setenv("FRAGSCAN_RUN", "0")
     base, names = _scan(fsb, layers, params, img, dt)
     for k, v in env.items():
         monkeypatch.setenv(k, v)
@@ -107,6 +109,28 @@ def test_same_values_on_every_tile_path(fsb, monkeypatch, env, dt):
         assert np.abs(got - base).max() <= (1e-5 if dt == "f32" else 2e-2) * np.abs(base).max()
     else:
         assert np.array_equal(got, base)
+
+
+@pytest.mark.parametrize("H,W,B", [(95, 95, 1), (96, 103, 1), (103, 110, 2), (128, 128, 1), (140, 333, 1),
+                                   (180, 180, 1), (230, 210, 1)])
+def test_small_grids(fsb, H, W, B):
+    """N4 on images whose grids leave the device part empty: 16- to 64-pixel
+    tiles, K in four parts, pools fused where the grid is smallest, fragments
+    of one to a few pixels (and empty ones); the whole map against the CPU
+    fragment method, and the profiled scan's map bit for bit."""
+    w = wl.WORKLOADS[2]
+    params, img = wl.workload_inputs(2, batch=B, height=H, width=W)
+    ref = oracle.frag_cpu.frag_scan(w.layers, params, img, w.patch)
+    net = fsb.Net(w.layers, params, 1)
+    print("small grid", (B, H, W), [L["name"] for L in net.launches(B, H, W)], flush=True)
+    x = torch.from_numpy(img).cuda()
+    got = net.scan(x).clone()
+    again = torch.full_like(got, float("nan"))
+    net.profile(x, reps=2, out=again)
+    torch.cuda.synchronize()
+    net.close()
+    assert torch.equal(got, again)
+    assert np.abs(got.cpu().numpy() - ref).max() <= 2e-6  # probabilities; float32 sums of 1200 terms behind a tanh
 
 
 def test_channels_of_any_scale(fsb, monkeypatch):
