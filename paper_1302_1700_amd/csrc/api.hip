@@ -1200,6 +1200,16 @@ fs_status make_plan(const fs_net *net, int B, int H, int W, Plan &P, const View 
             const size_t out_bytes = (size_t)B * o.Qy * o.Qx * std::max(o.hmax, 1) * std::max(o.wmax, 1) * o.C * es;
             buf = std::max(buf, out_bytes);
         }
+        if (L.type == 0 && !L.direct) {
+            ConvArgs &a = L.conv;
+            a.by_bands.set(a.nbands);
+            a.by_tiles.set(a.tiles_per_band);
+            a.by_F.set(a.F);
+            a.by_Qx.set(a.Qx);
+            a.by_Qy.set(a.Qy);
+            const int loads = L.vec ? l.cin * es / 16 : l.cin;
+            a.stage_px = 256 / loads;
+        }
         P.flops += L.flops;
         P.bytes += L.bytes;
         P.launches.push_back(L);

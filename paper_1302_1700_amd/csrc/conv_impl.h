@@ -412,30 +412,32 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
     // 8; the padding tiles exit).
     const int per_xcd = gridDim.x / 8;
     int bid = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-    const int nunit = RUN ? a.nfrag / a.F : a.nfrag;  // images (run tiles) or fragments
+    const int nunit = RUN ? a.by_F.quo(a.nfrag) : a.nfrag;  // images (run tiles) or fragments
     if (bid >= nunit * a.nbands * a.tiles_per_band) return;
     // the tile's channel blocks (weights, bias, last-layer weights) lie in the layer's packing
     if (!FS_DBG_OK(a.dbg, (int)(blockIdx.y + 1) * (WN * NB) <= a.nbt, DBG_CONV_WEIGHT)) return;
     int sib = 0;  // xsib: the fragment's column index
     if (!RUN && a.xsib) {
-        sib = bid % a.Qx;
-        bid /= a.Qx;
+        const int rest = a.by_Qx.quo(bid);
+        sib = bid - rest * a.Qx;
+        bid = rest;
     }
-    const int t = bid % a.tiles_per_band;
-    bid /= a.tiles_per_band;
-    const int band = bid % a.nbands;
+    const int tband = a.by_tiles.quo(bid);  // band of a fragment (xsib: of a row of fragments; run tiles: of an image)
+    const int t = bid - tband * a.tiles_per_band;
+    const int unit = a.by_bands.quo(tband);
+    const int band = tband - unit * a.nbands;
 
     // The tile's convolution outputs: segment 0 numbers them l in [l0, lend),
     // pixel l at row l / twb, column c0 + l % twb of fragment q's output; a
     // run tile that reaches the end of its fragment continues with the first
     // n1 pixels of the next fragment q1 (segment 1, width twb1).
-    int q, fy, fx, l0, lend, twb;
+    int q, fy, fx, l0, lend, twb, img;  // img: the image
     int q1 = 0, fy1 = 0, fx1 = 0, n1 = 0, twb1 = 1;
     int c0 = 0;
     int y0 = 0, rtM = 0, twM = 0;  // fused pool: max-filter rows [y0, y0 + rtM), columns [c0, c0 + twM)
     int hin, win;
     if constexpr (RUN) {
-        const int b = bid / a.nbands;
+        const int b = img = unit;
         const int p0 = t * a.mt;
         if (p0 >= a.run_pix) return;
         const int np = min(a.mt, a.run_pix - p0);
@@ -476,15 +478,16 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
         win = a.ext.x[fx];
     } else {
         if (a.xsib) {
-            const int row = bid / a.nbands;  // b * Qy + fy
-            fy = row % a.Qy;
+            img = a.by_Qy.quo(unit);  // unit: b * Qy + fy
+            fy = unit - img * a.Qy;
             fx = sib;
-            q = (row / a.Qy) * a.F + fy * a.Qx + fx;
+            q = img * a.F + fy * a.Qx + fx;
         } else {
-            q = bid / a.nbands;
-            const int rem = q % a.F;
-            fy = rem / a.Qx;
-            fx = rem - (rem / a.Qx) * a.Qx;
+            q = unit;
+            img = a.by_F.quo(q);
+            const int rem = q - img * a.F;
+            fy = a.by_Qx.quo(rem);
+            fx = rem - fy * a.Qx;
         }
         hin = a.ext.y[fy];
         win = a.ext.x[fx];
@@ -519,10 +522,14 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
         }
     }
     const int n0 = lend - l0;
-    const int yfirst = l0 / twb;
-    const int ylast = (lend - 1) / twb;
+    // (uniform quotients by a divisor known only here: Div, read back into a
+    // scalar register)
+    auto uquo = [](const Div &d, int n) { return __builtin_amdgcn_readfirstlane(d.quo(n)); };
+    const Div dtw(twb), dtw1(twb1);
+    const int yfirst = uquo(dtw, l0);
+    const int ylast = uquo(dtw, lend - 1);
     const int R = ylast - yfirst + a.ky;                     // window rows of segment 0
-    const int R1 = n1 > 0 ? (n1 - 1) / twb1 + a.ky : 0;      // then those of segment 1
+    const int R1 = n1 > 0 ? uquo(dtw1, n1 - 1) + a.ky : 0;   // then those of segment 1
     const int Cc = max(twb, n1 > 0 ? twb1 : 0) + a.kx - 1;   // window columns
     const int hin1 = n1 > 0 ? a.ext.y[fy1] : 0, win1 = n1 > 0 ? a.ext.x[fx1] : 0;
     const int CS = a.lds_cs;
@@ -561,13 +568,14 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
             // 48 -> 48 layers up to 0.9% faster than with eight); eight for
             // the rest, where two measured 3-4% slower.
             constexpr int UN = (!BF && VEC && NB >= 3 && (WN == 2 || WK == 2)) ? 2 : 8;
-            const int P = 256 / nvec;
+            const int P = a.stage_px;
             int p, v;
             Div(nvec).qr(threadIdx.x, p, v);
             if (p >= P) return;  // threads past P * nvec idle
             int r, c;
-            Div(Cc).qr(p, r, c);
-            const int dr = P / Cc, dc = P - dr * Cc;
+            const Div dcc(Cc);
+            dcc.qr(p, r, c);
+            const int dr = uquo(dcc, P), dc = P - dr * Cc;
             int soff = (gy0 + r) * rowp + __mul24(c0 + c, a.in_c) + v * width;
             const int sstep = dr * rowp + dc * a.in_c, swrap = rowp - Cc * a.in_c;
             // (split: the 16-byte slots 2w, 2w + 1 of a pixel, channels 8w .. 8w + 7,
@@ -618,7 +626,7 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
             }
         };
         if constexpr (VEC && !IN_F32) {
-            const int nvec = a.cin / LPE;
+            const int nvec = (unsigned)a.cin / LPE;
             if (SPLIT || nvec <= 64) {  // (the planner keeps split layers to 64 slots)
                 walk(nvec, LPE, [&](int off) { return *reinterpret_cast<const u4 *>(src + off); });
                 return;
@@ -704,8 +712,8 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
     // the step counters and LDS offsets of the K walk, its weight and bias
     // addresses) is computed once per wave in scalar registers
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wk = wv / WMN, wmn = wv - (wv / WMN) * WMN;
-    const int wm = wmn / WN, wn_raw = wmn - (wmn / WN) * WN;
+    const int wk = WK == 1 ? 0 : (unsigned)wv / WMN, wmn = (unsigned)wv % WMN;
+    const int wm = (unsigned)wmn / WN, wn_raw = (unsigned)wmn % WN;
     // Float32 layers whose two wave columns own unequal work -- the second
     // half ends in a padding block, whose products it skips (FC1 with the
     // fused head: 200 outputs in 14 blocks) -- swap the halves between the
@@ -721,7 +729,6 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
     // tile pixel m < npix: segment seg, output row y and column c0 + x of
     // fragment q (seg 0) or q1 (seg 1; c0 = 0 there)
     const int npix = n0 + n1;
-    const Div dtw(twb), dtw1(twb1);
     auto locate = [&](int m, int &seg, int &y, int &x) {
         seg = RUN && m >= n0;
         if (seg)
@@ -810,13 +817,18 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
         constexpr int NW = SPLIT ? 2 : 1;  // 16-byte operands per block and per pixel: (high, low) halves
         auto kwalk = [&](auto nbac) {
             constexpr int NBA = decltype(nbac)::value;
-            const int nh = a.cin / 16, nhs = a.ky * a.kx * nh;
+            const int nh = (unsigned)a.cin / 16, nhs = a.ky * a.kx * nh;
             const int s_begin = (a.ksteps * wk) / WK, nsteps = (a.ksteps * (wk + 1)) / WK - s_begin;
             // half step hs at tap column dx, channel group cc, window offset
             // pos; both halves of a step's offsets, one per lane
             int hs = 2 * s_begin;
-            int cc = hs % nh, dx = (hs / nh) % a.kx;
-            int pos = ((hs / nh) / a.kx * Cc + dx) * CS + cc * 16;
+            int cc = 0, dx = 0, pos = 0;
+            if constexpr (WK > 1) {
+                const int tap = uquo(Div(nh), hs), dy = uquo(Div(a.kx), tap);
+                cc = hs - tap * nh;
+                dx = tap - dy * a.kx;
+                pos = (dy * Cc + dx) * CS + cc * 16;
+            }
             const int tap_skip = CS - a.cin, row_skip = (Cc - a.kx) * CS;
             const bool upper = g >= 2;
             auto advance = [&] {
@@ -938,12 +950,18 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
             // cost a wave per SIMD)
             constexpr int PD = 2;
             static_assert(PD % 2 == 0, "the pixel double buffer needs an even unroll");
-            const int ncc = a.cin / KSTEP;
+            const int ncc = (unsigned)a.cin / KSTEP;
             const int s_begin = (a.ksteps * wk) / WK, s_end = (a.ksteps * (wk + 1)) / WK;
             const int nsteps = s_end - s_begin;
             // (branch-free: a straight-line loop body lets the compiler wait only
             // for the operands each product needs)
-            int cc = s_begin % ncc, dx = (s_begin / ncc) % a.kx, dy = (s_begin / ncc) / a.kx;
+            int cc = 0, dx = 0, dy = 0;
+            if constexpr (WK > 1) {
+                const int tap = uquo(Div(ncc), s_begin);
+                cc = s_begin - tap * ncc;
+                dy = uquo(Div(a.kx), tap);
+                dx = tap - dy * a.kx;
+            }
             auto advance = [&](int) {
                 ++cc;
                 const int w1 = cc == ncc;
@@ -1148,7 +1166,7 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
         if (own) fused_head_partials<ME, NB, WN, BF>(a, eacc, nb0, mb0, wn, lm, g, red);
         __syncthreads();
         fused_head_finish<WN>(
-            a, q / a.F, npix,
+            a, img, npix,
             [&](int m, int &hy, int &hx, int &y, int &x) {
                 int seg;
                 locate(m, seg, y, x);
@@ -1277,11 +1295,11 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
             // the next child row (o_y + 1, or o_y = 0 and ybar + 1).  With
             // fewer (column, chunk) pairs than threads the rows are shared
             // out as well.
-            const int nv = a.cout / TPAD;
+            const int nv = (unsigned)a.cout / TPAD;
             const int items = twM * nv;
-            const int nrg = max(1, 256 / items);   // row runs per (column, chunk)
-            const int rpt = (rtM + nrg - 1) / nrg;  // rows per run
             const Div dit(items), dnv(nv);
+            const int nrg = max(1, uquo(dit, 256));               // row runs per (column, chunk)
+            const int rpt = uquo(Div(nrg), rtM + nrg - 1);        // rows per run
             const long long d_oy = (long long)Qc * child_px * a.cout;  // next o_y: the child Qc fragments on
             const long long d_yb = (long long)a.pool_ow * a.cout;      // next ybar
             auto walk = [&](auto kc) {

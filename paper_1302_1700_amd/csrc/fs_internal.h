@@ -77,6 +77,24 @@ struct AxisTable {
     uint16_t x[kMaxAxis];
 };
 
+// Division of the workgroup and fragment numbers below 2^24 by a divisor fixed
+// for the launch, set up by the planner: n / d = (n * m) >> k with
+// k = 24 + ceil(log2 d) and m = ceil(2^k / d) (exact: m d - 2^k < d <=
+// 2^(k - 24), so n (m d - 2^k) < 2^k).  Three scalar instructions, where the
+// compiler's division by a kernel argument takes ~25 vector ones: about 350 of
+// the 870 vector instructions of a wave of the 16-channel 3x3 layers were such
+// divisions.
+struct UDiv {
+    uint32_t m, k;
+    void set(int d)
+    {
+        k = 24;
+        while ((1ull << (k - 24)) < (uint64_t)d) ++k;
+        m = (uint32_t)(((1ull << k) + d - 1) / d);
+    }
+    __host__ __device__ __forceinline__ int quo(int n) const { return (int)(((uint64_t)(uint32_t)n * m) >> k); }
+};
+
 // Fragment-batched convolution (also the fully connected layers, as
 // convolutions with k = size of the map they receive).
 struct ConvArgs {
@@ -98,6 +116,8 @@ struct ConvArgs {
     int band_w;           // output columns per band
     int nbands;           // bands per fragment
     int tiles_per_band;   // tiles per band (enough for the tallest fragment)
+    UDiv by_bands, by_tiles, by_F, by_Qx, by_Qy;  // / nbands, tiles_per_band, F, Qx, Qy
+    int stage_px;         // window pixels a workgroup stages at a time: 256 / (loads per pixel)
     int mt;               // output pixels per tile (16 * MB * 4 / (WN * WK))
     int tile_rows;        // > 0: a tile is tile_rows whole rows of its band (tile_rows * band_w <= mt)
     int lds_cs;           // channel stride of a pixel in LDS (elements)
