@@ -1097,13 +1097,16 @@ fs_status make_plan(const fs_net *net, int B, int H, int W, Plan &P, const View 
                 // workgroups the device needs for it
                 auto finish = [&](bool run, long long tiles, int &lds, int &gx) {
                     gx = (int)std::min<long long>((tiles + 7) / 8 * 8, kMaxGrid);
-                    // The FC layer with the fused head, when its register
-                    // tile fits only two workgroups per CU, ran 2-7% faster
-                    // one per CU on grids of at most 12 workgroups per CU
-                    // (N4 on 512x512 and 2x512x512 images; 3-5% slower on
-                    // larger grids; other layers, whose tiles fit three,
-                    // 12-18% slower): pad its LDS to admit one.
-                    if (fused_here && !L.hs && net->ncu > 0 && (long long)gx * L.gy <= 12LL * net->ncu &&
+                    // The 7 x 2 tile on float32 products with the fused head
+                    // ran 2-7% faster one workgroup per CU than two on
+                    // grids of at most 12 workgroups per CU (N4 on 512x512
+                    // and 2x512x512 images; 3-5% slower on larger grids):
+                    // pad its LDS to admit one.  Other tiles and the f16
+                    // products are faster at two (N4 mirrored 512x512,
+                    // split: 122 against 172 us; 16 -> 100 channels, 7 x 1,
+                    // 701x903: 89 against 106).
+                    if (fused_here && !L.hs && L.nb == 7 && L.wn == 2 && net->ncu > 0 &&
+                        (long long)gx * L.gy <= 12LL * net->ncu &&
                         conv_blocks_per_cu(net->dtype, g.is_image, L.mb, L.nb, L.wn, L.wk, L.vec, L.hs, run, lds) == 2)
                         lds = std::max(lds, (int)(kMaxLdsBytes / 2 + 1024));
                     // plan-only nets: 256 CUs, one workgroup each

@@ -87,6 +87,14 @@ __device__ __forceinline__ uint32_t bf16x2_key(uint32_t x)
     const uint32_t neg = __builtin_bit_cast(uint32_t, __builtin_bit_cast(s2v, x) >> (short)15);
     return x ^ (neg & 0x7fff7fffu);
 }
+// The larger of each half of two bf16 pairs within [-2^120, 2^120] (after a
+// tanh), straight from their bits: bf16 and f16 are both sign and magnitude, so
+// read as f16 the patterns keep their order (a NaN wins, as it does as a key).
+__device__ __forceinline__ uint32_t max_bf16x2_bounded(uint32_t a, uint32_t b)
+{
+    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_maximum(__builtin_bit_cast(h2, a), __builtin_bit_cast(h2, b)));
+}
 __device__ __forceinline__ uint32_t max_i16x2(uint32_t a, uint32_t b)
 {
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(s2v, a), __builtin_bit_cast(s2v, b)));
@@ -1182,9 +1190,12 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
     // with paired blocks in bf16, eight (16 bytes); other bf16 tiles hold 8
     // bytes per block.  Channels past c_out (padding blocks) and pixels past
     // the tile are not written.
+    // Written once for each activation where that pays (TANH: -1 decides per
+    // value at run time): bf16 tiles, whose launches wait for vector
+    // instructions.  Half-step tiles whose waves split K take a tanh in place,
+    // under one uniform branch (in the others that costs registers, and with
+    // them a wave per SIMD).
     const bool act_tanh = a.act == ACT_TANH;
-    // (half-step tiles whose waves split K: in place, under one uniform branch; in
-    // the others it costs registers, and with them a wave per SIMD)
     constexpr bool IN_PLACE = HS && WK > 1 && ME * NB <= 16;
     if constexpr (IN_PLACE) {
         if (act_tanh) {
@@ -1196,7 +1207,11 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
                     for (int e = 0; e < 4; ++e) eacc[i][j][e] = tanh_fast(eacc[i][j][e]);
         }
     }
-    auto act = [&](float v) { return !IN_PLACE && act_tanh ? tanh_fast(v) : v; };
+    auto epilogue = [&](auto tanhc) {
+    constexpr int TANH = decltype(tanhc)::value;
+    // bf16 pools compare tanh outputs as they are, others as order keys
+    constexpr bool KEYS = BF && TANH != 1;
+    auto act = [&](float v) { return TANH == 1 || (TANH < 0 && act_tanh) ? tanh_fast(v) : v; };
     constexpr bool PAIRED = BF && (NB % 2) == 0;
     constexpr int CRUN = PAIRED ? 8 : 4;  // consecutive channels per lane and block (pair)
 
@@ -1262,12 +1277,12 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
         // layer's stored (rounded) outputs.
         TC *tile = reinterpret_cast<TC *>(smem);
         __syncthreads();  // every wave is done with the window / partial sums
-        stage_tile(tile, true);
+        stage_tile(tile, KEYS);
         __syncthreads();
         const int kpy = a.pool_ky, kpx = a.pool_kx, ew = twb;
         const int Qc = a.Qx * kpx;
         const size_t child_px = (size_t)a.pool_oh * a.pool_ow;
-        const size_t cbase = (size_t)(q / a.F) * a.F * kpy * kpx;  // first child of image b
+        const size_t cbase = (size_t)img * a.F * kpy * kpx;  // first child of image b
         const Div dky(kpy), dkx(kpx), dtm(twM);
         auto child_ptr = [&](int r, int c) {
             int ybar, oy, xbar, ox;
@@ -1318,15 +1333,17 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
                     auto vmax = [&](u4 m, const u4 x) {
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
-                            if constexpr (BF)
+                            if constexpr (KEYS)
                                 m[e] = max_i16x2(m[e], x[e]);
+                            else if constexpr (BF)
+                                m[e] = max_bf16x2_bounded(m[e], x[e]);
                             else
                                 m[e] = __float_as_uint(fmaxf(__uint_as_float(m[e]), __uint_as_float(x[e])));
                         }
                         return m;
                     };
                     auto put = [&](u4 m, int r) {
-                        if constexpr (BF) {
+                        if constexpr (KEYS) {
 #pragma unroll
                             for (int e = 0; e < 4; ++e) m[e] = bf16x2_key(m[e]);
                         }
@@ -1397,12 +1414,14 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
                 for (int i = 0; i < kpy; ++i)
                     for (int j = 0; j < kpx; ++j) {
                         const TC x = src[__mul24(__mul24(i, ew) + j, TS)];
-                        if constexpr (BF)
+                        if constexpr (KEYS)
                             m = (TC)max_i16x2(m, x);  // keys in the low half
+                        else if constexpr (BF)
+                            m = (TC)max_bf16x2_bounded(m, x);
                         else
                             m = fmaxf(m, x);
                     }
-                if constexpr (BF) m = (TC)bf16x2_key(m);
+                if constexpr (KEYS) m = (TC)bf16x2_key(m);
                 if (child_ok(r, c)) child_ptr(r, c)[ch] = m;
             }
         }
@@ -1517,6 +1536,17 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
                 }
             }
         }
+    }
+    };
+    if constexpr (IN_PLACE) {
+        epilogue(std::integral_constant<int, 0>());
+    } else if constexpr (BF) {
+        if (act_tanh)
+            epilogue(std::integral_constant<int, 1>());
+        else
+            epilogue(std::integral_constant<int, 0>());
+    } else {
+        epilogue(std::integral_constant<int, -1>());
     }
 }
 
