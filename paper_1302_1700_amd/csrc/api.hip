@@ -804,41 +804,30 @@ long long count_tiles(const Geo &in, int ky, int kx, int B, int mt, long long li
     return n;
 }
 
-// Register tile of a split float32 layer on a grid that does not fill the
-// device: the fewest pixels per workgroup that still leave it few enough
-// workgroups per CU, since there a launch takes as long as one workgroup's
-// walk over K.  48 -> 48 layers (3 blocks, split K) go from 128 pixels and two
-// K parts to 64 or 32 pixels and four; FC layers of 129-224 outputs (7 x 2)
-// to 16 or 32 pixels (four waves across the channels).  Measured on N4, us per launch, 128 / 64 / 32 pixels
-// (the grid of 64-pixel tiles in workgroups): 5x5 on 103x110 (~170) 14.5 /
-// 10.8 / 11.0, on 128^2 (240) 15.0 / 11.4 / 11.9, on 180^2 (430) 16.5 / 15.2 /
-// 20.1, on 256^2 (915) 24.5 / 25.5 / 34.0; last 4x4 on 128^2 (64; 128 of 32
-// pixels) 11.0 / 8.5 / 7.7, on 256^2 (640) 18.4 / 15.9 / 22.3.  FC1 + head, 128
-// / 32 / 16 pixels: 128^2 (256 fragments of 4-9 pixels) 20.6 / 11.0 / 10.2, 180^2
-// (25-36) 20.9 / 14.4 / 23.1, 256^2 (100-121) 21.4 / 28.6 / 45.9.
+// Pixels per tile of a split float32 layer on a grid that does not fill the
+// device: the fewest that leave it at most one workgroup per CU, since there
+// a launch takes as long as one workgroup's walk over K.  Only the pixel
+// blocks per wave change, never how the waves share K or the channels, so
+// every output is the same sum in the same order at every size (a tiled scan
+// gives the whole scan's map bit for bit).  Measured on N4, us per launch:
+//   48 -> 48, 128 against 64 pixels (64-pixel workgroups): 103x110 5x5 (~170)
+//   14.7 / 11.4, 4x4 11.9 / 9.5 and 10.4 / 8.7; 180^2 last 4x4 (256) 12.2 / 10.0,
+//   5x5 (430) 16.5 / 16.8; 256^2 5x5 (915) 24.5 / 28.4;
+//   FC1 + head, 128 / 64 / 32 pixels: 128^2 (256 fragments of 4-9 pixels) 20.6 /
+//   13.9 / 12.3, 180^2 (25-36) 20.8 / 13.8 / 19.0, 256^2 (100-121) 21.5 / 22.0 / 37.
 void small_grid_tile(const fs_net *net, int li, const Geo &in, int B, NetLayer &l)
 {
     if (!l.hs || net->dtype != DT_F32 || tile_override(li, nullptr, nullptr, nullptr, nullptr)) return;
     if (const char *e = getenv("FRAGSCAN_RUN"); e && e[0]) return;  // run tiles forced on or off: the layer's own tile
+    const bool narrow = l.nb == 3 && l.wn == 1 && l.wk == 2;  // 48 -> 48 layers: 3 blocks, K in two
+    const bool wide = l.nb == 7 && l.wn == 2 && l.wk == 1 && one_group(l) && !getenv("FRAGSCAN_WIDE");  // 129-224 outputs
+    if (!narrow && !wide) return;
     const int ncu = net->ncu > 0 ? net->ncu : 256;
-    struct Shape { int mb, nb, wn, wk, quarters; };  // at most quarters / 4 workgroups per CU
-    static const Shape narrow[] = {{2, 3, 1, 4, 3}, {4, 3, 1, 4, 10}};
-    static const Shape wide[] = {{1, 4, 4, 1, 8}, {2, 4, 4, 1, 8}};
-    const Shape *s = nullptr;
-    int n = 0;
-    if (l.nb == 3 && l.wn == 1 && l.wk == 2 && l.ksteps_h >= 4)
-        s = narrow, n = 2;
-    else if (l.nb == 7 && l.wn == 2 && l.wk == 1 && one_group(l) && !getenv("FRAGSCAN_WIDE"))
-        s = wide, n = 2;
-    for (int i = 0; i < n; ++i) {
-        const long long most = (long long)ncu * s[i].quarters / 4;
-        if (count_tiles(in, l.k, l.kx, B, 16 * s[i].mb * 4 / (s[i].wn * s[i].wk), most) > most) continue;
-        l.mb = s[i].mb;
-        l.nb = s[i].nb;
-        l.wn = s[i].wn;
-        l.wk = s[i].wk;
-        return;
-    }
+    for (int mb = narrow ? 2 : 1; mb <= 2; ++mb)
+        if (count_tiles(in, l.k, l.kx, B, 16 * mb * 4 / (l.wn * l.wk), ncu) <= ncu) {
+            l.mb = mb;
+            return;
+        }
 }
 
 // Whether the pool after conv layer li goes into the convolution's epilogue.
@@ -849,9 +838,9 @@ void small_grid_tile(const fs_net *net, int li, const Geo &in, int B, NetLayer &
 // c_in k^2 ov < elem * (peak FLOP/s / HBM bytes/s): every layer of the five
 // workloads except N4's 48 -> 48 convolutions, whose fused form measured
 // 10-35% slower.  FRAGSCAN_POOL_FUSE=1 / 0 forces it on / off.
-// small: the layer's grid of 64-pixel tiles is at most one workgroup per CU;
-// the separate pool's launch costs more there than the recomputed halo (N4 on
-// 103x110: 60 -> 54 us a scan, 128^2 66 -> 62; 180^2, 430 workgroups, the same).
+// small: small_grid_tile chose 64-pixel tiles; the separate pool's launch costs
+// more there than the recomputed halo (N4 on 103x110: 69 -> 55 us a scan, 128^2
+// 74 -> 61, 180^2, the last 4x4 only, 13.4 us either way).
 bool want_pool_fusion(const fs_net *net, int li, const NetLayer &l, bool small)
 {
     const int nl = (int)net->L.size();
@@ -1004,9 +993,7 @@ fs_status make_plan(const fs_net *net, int B, int H, int W, Plan &P, const View 
                 if (l.hs) l.ksteps = l.ksteps_h;
             }
             small_grid_tile(net, li, g, B, l);
-            const bool small = l.mb > 0 && l.wk == 4 &&
-                               count_tiles(g, ky, kx, B, 64, net->ncu > 0 ? net->ncu : 256) <=
-                                   (net->ncu > 0 ? net->ncu : 256);
+            const bool small = l.mb > 0 && l.wk == 2;
             L.vec = l.vec;
             L.hs = l.hs;
             L.nb = l.nb;
@@ -1041,7 +1028,6 @@ fs_status make_plan(const fs_net *net, int B, int H, int W, Plan &P, const View 
             const char *dv = getenv("FRAGSCAN_DIRECT");
             const bool want_direct = dv ? dv[0] == '1' : l.cout <= 16;
             const bool pool_fuse = !fused_here && want_pool_fusion(net, li, l, small);
-            if (pool_fuse && small) l.mb = 4;  // 64 pixels: room for the halo
             if (l.has_w32 && !fused_here && !pool_fuse && want_direct) {
                 L.direct = true;
                 L.conv.lds_bytes = 0;
@@ -1753,9 +1739,6 @@ static fs_status net_create(const fs_layer *layers, int32_t n_layers, int32_t in
         }
         const int grp = l.nb * l.wn;
         l.nbt = (nbt0 + grp - 1) / grp * grp;
-        // (16 blocks, so that small grids can take the same weights with four
-        // waves of four across the channels)
-        if (dtype == FS_F32 && l.vec && l.nb == 7 && l.wn == 2 && l.nbt == 14) l.nbt = 16;
         l.ksteps = (l.k * l.kx * l.cin + KSTEP - 1) / KSTEP;
         if (l.ksteps < l.wk) {  // every K-splitting wave needs at least one step
             delete net;

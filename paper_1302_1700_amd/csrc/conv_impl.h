@@ -399,7 +399,7 @@ constexpr int half_step_ring(int mb, int nb, bool bf)
 {
     const int cycles = mb * nb * 16 * (bf ? 1 : 3);
     if (mb * nb >= 12) return 1;
-    return cycles >= 384 || (mb == 4 && nb == 1) ? 2 : 4;
+    return cycles >= 336 || (mb == 4 && nb == 1) ? 2 : 4;
 }
 
 template <int MB, int NB, int WN, int WK, bool BF, bool IN_F32, bool VEC, bool RUN, bool HS>
@@ -1600,9 +1600,8 @@ hipError_t launch_one(const ConvArgs &a, int gx, int gy, hipStream_t s)
 #define FS_CONV_TILES_HS(X)                                                                     \
     X(1, 1, 1, 1) X(1, 2, 1, 1) X(1, 3, 1, 1) X(1, 4, 1, 1) X(2, 1, 1, 1) X(2, 2, 1, 1)          \
     X(2, 3, 1, 1) X(2, 4, 1, 1) X(4, 1, 1, 1) X(4, 2, 1, 1) X(4, 3, 1, 1) X(4, 4, 1, 1)          \
-    X(2, 7, 1, 1) X(4, 7, 1, 1) X(2, 7, 2, 1) X(4, 7, 2, 1) X(4, 4, 2, 1)          \
-    X(1, 4, 4, 1) X(2, 4, 4, 1) X(4, 4, 4, 1) X(2, 3, 1, 2) X(4, 3, 1, 2)                          \
-    X(1, 3, 1, 4) X(2, 3, 1, 4) X(4, 3, 1, 4)
+    X(2, 3, 1, 2) X(4, 3, 1, 2) X(2, 7, 1, 1) X(4, 7, 1, 1) X(1, 7, 2, 1)          \
+    X(2, 7, 2, 1) X(4, 7, 2, 1) X(2, 4, 2, 1) X(4, 4, 2, 1)
 #define FS_CONV_TILES_RUN_HS(X) \
     X(2, 2, 1, 1) X(4, 2, 1, 1) X(4, 3, 1, 1) X(4, 3, 1, 2) X(4, 4, 1, 1) X(4, 7, 1, 1) X(4, 7, 2, 1)
 

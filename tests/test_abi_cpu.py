@@ -729,10 +729,10 @@ def test_small_grid_tiles(monkeypatch):
     net = _plan_net(wl.n4_layers())
     tile = lambda H: {L["layer"]: L["name"].split("<")[1].split(", false")[0] + ("+pool" if "+pool" in L["name"] else "")
                       for L in net.launches(1, H, H) if L["kind"] == 0}
-    assert tile(128) == {0: "4, 3, 1, 1+pool", 2: "4, 3, 1, 4+pool", 4: "4, 3, 1, 4+pool", 6: "4, 3, 1, 4+pool",
-                         8: "1, 4, 4, 1"}
+    assert tile(128) == {0: "4, 3, 1, 1+pool", 2: "2, 3, 1, 2+pool", 4: "2, 3, 1, 2+pool", 6: "2, 3, 1, 2+pool",
+                         8: "1, 7, 2, 1"}
     mid = tile(180)
-    assert (mid[2], mid[4], mid[8]) == ("4, 3, 1, 4", "4, 3, 1, 4", "2, 4, 4, 1")
+    assert (mid[2], mid[4], mid[6], mid[8]) == ("4, 3, 1, 2", "4, 3, 1, 2", "2, 3, 1, 2+pool", "2, 7, 2, 1")
     big = tile(512)
     assert {big[i] for i in (2, 4, 6)} == {"4, 3, 1, 2"} and big[8] == "4, 7, 2, 1"
     assert net.plan(1, 128, 128)["n_launches"] == 5 and net.plan(1, 512, 512)["n_launches"] == 8

@@ -97,8 +97,6 @@ def test_same_values_on_every_tile_path(fsb, monkeypatch, env, dt):
     w0 = ix.patch_size(layers)
     params = wl.make_weights(layers, 9, 0.08)
     img = wl.make_image(10, 2, w0 + 121, w0 + 108, 1)
-    if "FRAGSCAN_RUN" in env:  # (a small grid takes another split of K unless run tiles are forced off or on)
-        monkeypatch.setenv("FRAGSCAN_RUN", "0")
     base, names = _scan(fsb, layers, params, img, dt)
     for k, v in env.items():
         monkeypatch.setenv(k, v)
@@ -115,7 +113,7 @@ def test_same_values_on_every_tile_path(fsb, monkeypatch, env, dt):
                                    (180, 180, 1), (230, 210, 1)])
 def test_small_grids(fsb, H, W, B):
     """N4 on images whose grids leave the device part empty: 16- to 64-pixel
-    tiles, K in four parts, pools fused where the grid is smallest, fragments
+    tiles, pools fused where the grid is smallest, fragments
     of one to a few pixels (and empty ones); the whole map against the CPU
     fragment method, and the profiled scan's map bit for bit."""
     w = wl.WORKLOADS[2]
@@ -131,6 +129,25 @@ def test_small_grids(fsb, H, W, B):
     net.close()
     assert torch.equal(got, again)
     assert np.abs(got.cpu().numpy() - ref).max() <= 2e-6  # probabilities; float32 sums of 1200 terms behind a tanh
+
+
+@pytest.mark.parametrize("H,W,tile", [(512, 480, (100, 130)), (300, 333, (40, 240)), (260, 260, (9, 11))])
+def test_tiles_of_other_sizes_give_the_same_sums(fsb, H, W, tile):
+    """A tiled scan whose tiles take other register tiles (and fuse other
+    pools) than the whole image's scan gives its map bit for bit."""
+    w = wl.WORKLOADS[2]
+    params, img = wl.workload_inputs(2, height=H, width=W)
+    net = fsb.Net(w.layers, params, 1)
+    x = torch.from_numpy(img).cuda()
+    ref = net.scan(x).clone()
+    whole = [L["name"] for L in net.launches(1, H, W)]
+    part = [L["name"] for L in net.launches(1, tile[0] + 94, tile[1] + 94)]
+    assert whole != part
+    print("tiled sums", (H, W), tile, whole, part, flush=True)
+    got = net.scan_tiled(x, tile)
+    torch.cuda.synchronize()
+    net.close()
+    assert torch.equal(got, ref)
 
 
 def test_channels_of_any_scale(fsb, monkeypatch):
