@@ -42,7 +42,21 @@ PEAK = {  # MI355X published dense peaks
     "hbm_gbs": 8000.0,
     "f32_tflops": 157.3,
     "bf16_tflops": 2516.6,
+    # float32 layers on the f16 matrix cores (f16 peak = bf16 peak): three
+    # products per float32 product
+    "split_tflops": 2516.6 / 3,
 }
+
+
+def matrix_peak(launch, dtype):
+    """Peak TFLOP/s of a launch's matrix products.  The last parameter of a
+    convolution kernel's name says whether it walks K in half steps, which
+    float32 layers do on pairs of f16 values."""
+    if dtype == "bf16":
+        return PEAK["bf16_tflops"]
+    name = launch["name"].split("+")[0]  # "+pool", "+head": what the launch fuses
+    split = name.startswith("conv_frag_mfma<") and name.endswith("true>")
+    return PEAK["split_tflops"] if split else PEAK["f32_tflops"]
 
 
 def measured_traffic(launch_name, layer, workload):
@@ -228,9 +242,9 @@ def main():
         xe = torch.zeros((w.batch, eh, ew, w.channels), dtype=torch.float32, device="cuda")
         xe[:, :w.height, :w.width] = x
         per = net.profile(xe, reps=args.profile_reps)
-    peak_mm = PEAK["bf16_tflops"] if w.dtype == "bf16" else PEAK["f32_tflops"]
     rows = []
     for L, t in zip(launches, per):
+        peak_mm = matrix_peak(L, w.dtype)
         r = {"name": L["name"], "layer": L["layer"], "ms": t, "flops": L["flops"], "bytes": L["bytes"],
              "tflops": L["flops"] / (t * 1e-3) / 1e12 if t > 0 else 0.0,
              "gbs": L["bytes"] / (t * 1e-3) / 1e9 if t > 0 else 0.0}
@@ -243,6 +257,9 @@ def main():
     conv_flops = sum(r["flops"] for r in rows)
     conv_ms = sum(r["ms"] for r in rows if r["flops"] > 0)
     traffic = measured_traffic(dom["name"], dom["layer"], w.name) if border == "valid" else None
+    peak_mm = matrix_peak(dom, w.dtype)
+    # matrix-core time of the scan's products at the peak rate of each launch
+    peak_ms = sum(r["flops"] / (matrix_peak(r, w.dtype) * 1e12) for r in rows) * 1e3 * plan["flops"] / max(conv_flops, 1.0)
     if dom["bound"] == "mfma":
         roof = {"bound": "mfma", "achieved": dom["tflops"], "peak": peak_mm, "unit": "TFLOP/s",
                 "frac": dom["tflops"] / peak_mm}
@@ -274,7 +291,7 @@ def main():
                    "workspace_bytes": ws.numel()},
         "host_enqueue_ms_per_step": host_ms,
         "tflops": plan["flops"] / (ms * 1e-3) / 1e12,
-        "pct_mfma_peak": 100.0 * plan["flops"] / (ms * 1e-3) / 1e12 / peak_mm,
+        "pct_mfma_peak": 100.0 * peak_ms / ms,
         "conv_tflops_in_conv_kernels": conv_flops / (conv_ms * 1e-3) / 1e12 if conv_ms else 0.0,
         "roofline": roof,
         "launches": rows,
