@@ -89,11 +89,14 @@ __device__ __forceinline__ uint32_t bf16x2_key(uint32_t x)
 }
 // The larger of each half of two bf16 pairs within [-2^120, 2^120] (after a
 // tanh), straight from their bits: bf16 and f16 are both sign and magnitude, so
-// read as f16 the patterns keep their order (a NaN wins, as it does as a key).
+// read as f16 the patterns keep their order.  A NaN (quiet in bf16, so quiet
+// as f16) loses to any number, as in the float32 pools; the builtin maxima
+// either let it win or first canonicalise both operands.
 __device__ __forceinline__ uint32_t max_bf16x2_bounded(uint32_t a, uint32_t b)
 {
-    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_maximum(__builtin_bit_cast(h2, a), __builtin_bit_cast(h2, b)));
+    uint32_t m;
+    asm("v_pk_max_f16 %0, %1, %2" : "=v"(m) : "v"(a), "v"(b));
+    return m;
 }
 __device__ __forceinline__ uint32_t max_i16x2(uint32_t a, uint32_t b)
 {

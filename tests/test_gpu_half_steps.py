@@ -217,3 +217,34 @@ def test_non_finite_pixels_stay_in_their_windows(fsb):
     Y, X = np.meshgrid(np.arange(got.shape[1]), np.arange(got.shape[2]), indexing="ij")
     clean = (Y > 20) | (Y + w0 - 1 < 20) | (X > 17) | (X + w0 - 1 < 17)
     assert np.isfinite(got[0][clean]).all()
+
+
+@pytest.mark.parametrize("net", [2, 3, 5])
+def test_nan_pixels_lose_in_every_pool(fsb, monkeypatch, net):
+    """A NaN pixel makes NaN of the outputs whose pools hold nothing else: the
+    same windows in float32 and bf16, with pools fused and separate."""
+    layers = wl.WORKLOADS[net].layers
+    w0 = ix.patch_size(layers)
+    rng = np.random.default_rng(net)
+    params = []
+    for L in layers:
+        if L["kind"] == "pool":
+            params.append(None)
+        else:
+            shape = (L["c_out"], L["c_in"], L["k"], L["k"])
+            params.append((rng.normal(0.0, 1.0 / np.sqrt(np.prod(shape[1:])), shape).astype(np.float32),
+                           np.zeros(L["c_out"], np.float32)))
+    c = layers[0]["c_in"]
+    img = wl.make_image(net, 1, w0 + 60, w0 + 71, c)
+    img[0, 60, 70, 0] = img[0, 61, 3, c - 1] = np.nan
+    img[0, 5, 77, 0] = np.uint32(0xffc00000).view(np.float32)  # its sign bit set
+    masks = {}
+    for dt in ("f32", "bf16"):
+        for fuse in ("1", "0"):
+            monkeypatch.setenv("FRAGSCAN_POOL_FUSE", fuse)
+            print("NaN pixels", net, dt, fuse, flush=True)
+            got, _ = _scan(fsb, layers, params, img, dt)
+            masks[dt, fuse] = np.isnan(got)
+    assert 0 < masks["f32", "0"].sum() < masks["f32", "0"].size
+    for k, m in masks.items():
+        assert np.array_equal(m, masks["f32", "0"]), (k, m.sum(), masks["f32", "0"].sum())
