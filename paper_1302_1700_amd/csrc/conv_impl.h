@@ -136,9 +136,14 @@ struct Div {
 
 // tanh(x) = 1 - 2 / (exp(2x) + 1), with the hardware exp2 and reciprocal:
 // absolute error a few 1e-7, saturates cleanly to +-1 for large |x|.
+constexpr float kTanhScale = 2.8853900817779268f;  // exp2(x * this) = exp(2x)
+// PRE: x comes multiplied by kTanhScale already (split layers, whose sums are
+// multiplied by a power of two per channel anyway: the same product, rounded
+// once, and one vector instruction less per value).
+template <bool PRE = false>
 __device__ __forceinline__ float tanh_fast(float x)
 {
-    const float t = __builtin_amdgcn_exp2f(x * 2.8853900817779268f);  // exp(2x)
+    const float t = __builtin_amdgcn_exp2f(PRE ? x : x * kTanhScale);
     return 1.0f - 2.0f * __builtin_amdgcn_rcpf(t + 1.0f);
 }
 
@@ -194,7 +199,8 @@ __device__ __forceinline__ bool head_two_class(const ConvArgs &a)
     return !(BF && NB % 2 == 0) && a.head_ncls == 2 && a.head_act == ACT_SOFTMAX;
 }
 
-template <int MB, int NB, int WN, bool BF>
+// PRE: the sums are those tanh_fast<true> takes where the activation is tanh.
+template <int MB, int NB, int WN, bool BF, bool PRE>
 __device__ __forceinline__ void fused_head_partials(const ConvArgs &a, const f4 (&acc)[MB][NB], int nb0, int mb0,
                                                     int wn, int lm, int g, float *red)
 {
@@ -254,7 +260,7 @@ __device__ __forceinline__ void fused_head_partials(const ConvArgs &a, const f4 
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     float v = acc[i][j][e];
-                    if (a.act == ACT_TANH) v = tanh_fast(v);
+                    if (a.act == ACT_TANH) v = tanh_fast<PRE>(v);
                     part[i][0] = fmaf(w1[e] - w0[e], v, part[i][0]);
                 }
         }
@@ -283,7 +289,7 @@ __device__ __forceinline__ void fused_head_partials(const ConvArgs &a, const f4 
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     float v = acc[i][j][e];
-                    if (a.act == ACT_TANH) v = tanh_fast(v);
+                    if (a.act == ACT_TANH) v = tanh_fast<PRE>(v);
 #pragma unroll
                     for (int c = 0; c < NC; ++c) part[i][c] = fmaf(w2[c][e], v, part[i][c]);
                 }
@@ -1161,10 +1167,12 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
             }
     }
     if constexpr (SPLIT) {
-        // back from the operands' power-of-two scales (exact)
+        // back from the operands' power-of-two scales (exact), on to the
+        // exponent a tanh needs
+        const float to = a.act == ACT_TANH ? kTanhScale : 1.f;
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
-            const f4 us = *reinterpret_cast<const f4 *>(a.unscale + (nb0 + j) * 16 + 4 * g);
+            const f4 us = to * *reinterpret_cast<const f4 *>(a.unscale + (nb0 + j) * 16 + 4 * g);
 #pragma unroll
             for (int i = 0; i < ME; ++i) eacc[i][j] *= us;
         }
@@ -1174,7 +1182,7 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
     if (a.head_ncls > 0) {
         float *red = reinterpret_cast<float *>(smem);
         __syncthreads();  // the LDS window / partial sums (which red reuses) are no longer read
-        if (own) fused_head_partials<ME, NB, WN, BF>(a, eacc, nb0, mb0, wn, lm, g, red);
+        if (own) fused_head_partials<ME, NB, WN, BF, SPLIT>(a, eacc, nb0, mb0, wn, lm, g, red);
         __syncthreads();
         fused_head_finish<WN>(
             a, img, npix,
@@ -1207,14 +1215,14 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
 #pragma unroll
                 for (int j = 0; j < NB; ++j)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) eacc[i][j][e] = tanh_fast(eacc[i][j][e]);
+                    for (int e = 0; e < 4; ++e) eacc[i][j][e] = tanh_fast<SPLIT>(eacc[i][j][e]);
         }
     }
     auto epilogue = [&](auto tanhc) {
     constexpr int TANH = decltype(tanhc)::value;
     // bf16 pools compare tanh outputs as they are, others as order keys
     constexpr bool KEYS = BF && TANH != 1;
-    auto act = [&](float v) { return TANH == 1 || (TANH < 0 && act_tanh) ? tanh_fast(v) : v; };
+    auto act = [&](float v) { return TANH == 1 || (TANH < 0 && act_tanh) ? tanh_fast<SPLIT>(v) : v; };
     constexpr bool PAIRED = BF && (NB % 2) == 0;
     constexpr int CRUN = PAIRED ? 8 : 4;  // consecutive channels per lane and block (pair)
 
