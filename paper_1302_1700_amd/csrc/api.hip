@@ -1027,22 +1027,32 @@ fs_status make_plan(const fs_net *net, int B, int H, int W, Plan &P, const View 
             // it for every layer it supports, =0 for none.
             const char *dv = getenv("FRAGSCAN_DIRECT");
             const bool want_direct = dv ? dv[0] == '1' : l.cout <= 16;
-            const bool pool_fuse = !fused_here && want_pool_fusion(net, li, l, small);
-            if (l.has_w32 && !fused_here && !pool_fuse && want_direct) {
-                L.direct = true;
-                L.conv.lds_bytes = 0;
-            } else {
+            bool pool_fuse = !fused_here && want_pool_fusion(net, li, l, small);
+            auto plan_tiles = [&](bool with_pool) {
                 fs_status st = FS_OK;
                 // (bf16 layers with an odd multiple of 16 input channels
                 // could do without the padding before they took the vector
                 // path: their largest windows still can)
                 for (bool packed : {false, true}) {
                     if (packed && !(net->dtype == DT_BF16 && l.hs)) break;
-                    st = pool_fuse ? plan_conv_pool_tiles(net, l, g, net->L[li + 1].k, net->L[li + 1].kx, L, packed)
+                    st = with_pool ? plan_conv_pool_tiles(net, l, g, net->L[li + 1].k, net->L[li + 1].kx, L, packed)
                                    : plan_conv_tiles(net, l, g, L, false, packed);
                     if (st == FS_OK) break;
                 }
-                if (st != FS_OK) return st;
+                return st;
+            };
+            // A pool window of more outputs than any tile holds (64 on the
+            // small grids, 128 to 512 elsewhere), or whose tile does not fit
+            // in LDS: the pool runs by itself.
+            if (pool_fuse && plan_tiles(true) != FS_OK) pool_fuse = false;
+            if (l.has_w32 && !fused_here && !pool_fuse && want_direct) {
+                L.direct = true;
+                L.conv.lds_bytes = 0;
+            } else {
+                if (!pool_fuse) {
+                    fs_status st = plan_tiles(false);
+                    if (st != FS_OK) return st;
+                }
                 // The float32 FC layer with the fused head on a grid that
                 // runs it one workgroup per CU (the rule below), with 14
                 // blocks of 16 for at most 208 channels (200 in N4): the
@@ -1331,8 +1341,10 @@ fs_status get_plan(const fs_net *net, int B, int H, int W, std::shared_ptr<const
             }
     }
     auto P = std::make_shared<Plan>();
+    const std::string err = g_err;
     fs_status st = make_plan(net, B, H, W, *P, view);
     if (st != FS_OK) return st;
+    g_err = err;  // (tilings that were tried and did not fit are no failure of the call)
     out = P;
     if (c) {
         std::lock_guard<std::mutex> lock(c->mu);

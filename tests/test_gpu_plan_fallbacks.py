@@ -1,0 +1,49 @@
+"""Scans whose layers fall back to another tiling (or stay off a slower one):
+maps against the CPU fragment method."""
+import numpy as np
+import pytest
+
+import oracle
+from oracle import index as ix
+from paper_1302_1700_amd import workloads as wl
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def fsb():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1302_1700_amd import fragscan
+    fragscan.load()
+    return fragscan
+
+
+def _check(fsb, layers, dt, more, seed):
+    """Probabilities against the oracle: float32 sums of up to ~1000 terms
+    behind a tanh, or a few roundings to 8 significand bits per value."""
+    h0, w0 = ix.patch_hw(layers)
+    sigma = [1.0 / np.sqrt(L["c_in"] * L["k"] * (L.get("kx") or L["k"])) for L in layers if L["kind"] != "pool"]
+    params = wl.make_weights(layers, seed, float(np.mean(sigma)))
+    img = wl.make_image(seed + 1, 2, h0 + more[0], w0 + more[1], layers[0]["c_in"])
+    ref = oracle.frag_cpu.frag_scan(layers, params, img, (h0, w0))
+    net = fsb.Net(layers, params, layers[0]["c_in"], 0, dt)
+    names = [L["name"] for L in net.launches(*img.shape[:3])]
+    print("fallback", dt, img.shape, names, flush=True)
+    got = net.scan(torch.from_numpy(img).cuda())
+    torch.cuda.synchronize()
+    net.close()
+    assert np.abs(got.cpu().numpy() - ref).max() <= (2e-6 if dt == "f32" else 3e-2)
+    return names
+
+
+@pytest.mark.parametrize("dt,cin,cout,ky,kx", [("f32", 48, 48, 8, 8), ("f32", 48, 48, 9, 9), ("f32", 48, 40, 3, 22),
+                                               ("f32", 48, 48, 2, 33), ("bf16", 16, 128, 12, 12),
+                                               ("bf16", 48, 200, 17, 9)])
+def test_pools_beyond_a_fused_tile(fsb, dt, cin, cout, ky, kx):
+    layers = [wl.conv(2, 1, cin), wl.conv(3, cin, cout), wl.pool(ky, cout, kx=kx), wl.fc(1, cout, 20),
+              wl.fc(1, 20, 3, "softmax")]
+    names = _check(fsb, layers, dt, (21, 30), ky + kx)
+    if ky * kx > 64:
+        assert any(n.startswith("pool_") for n in names), names

@@ -1,0 +1,65 @@
+"""Planner rules with more than one way to run a layer: the way that has no
+tile must not refuse the net (CPU, planning-only handles: 256 CUs)."""
+import numpy as np
+import pytest
+
+from oracle import index as ix
+from paper_1302_1700_amd import fragscan as fsb
+from paper_1302_1700_amd import workloads as wl
+
+
+@pytest.fixture(autouse=True)
+def _no_switches(monkeypatch):
+    for v in ("FRAGSCAN_TILE", "FRAGSCAN_RUN", "FRAGSCAN_POOL_FUSE", "FRAGSCAN_SPLIT", "FRAGSCAN_WIDE",
+              "FRAGSCAN_STORE", "FRAGSCAN_LDS_PAD", "FRAGSCAN_ROWTILES", "FRAGSCAN_NO_FUSED_HEAD"):
+        monkeypatch.delenv(v, raising=False)
+
+
+def _net(layers, dt="f32"):
+    return fsb.Net(layers, wl.make_weights(layers, 0, 0.1), layers[0]["c_in"], 0, dt, plan_only=True)
+
+
+WIDE_POOLS = [(8, 8), (9, 9), (10, 10), (12, 12), (16, 16), (3, 22), (2, 33)]
+
+
+@pytest.mark.parametrize("ky,kx", WIDE_POOLS)
+@pytest.mark.parametrize("side", [60, 100, 130, 400])
+def test_wide_pools_at_every_size(ky, kx, side):
+    """A pool whose window holds more outputs than a small grid's 64-pixel
+    tile runs by itself, as on larger images: the same net plans at every
+    size that holds its window."""
+    layers = [wl.conv(4, 1, 48), wl.conv(3, 48, 48), wl.pool(ky, 48, kx=kx), wl.fc(2, 48, 200),
+              wl.fc(1, 200, 2, "softmax")]
+    h0, w0 = ix.patch_hw(layers)
+    H, W = max(side, h0), max(side, w0)
+    net = _net(layers)
+    ls = net.launches(1, H, W)
+    assert net.plan(1, H, W)["out_h"] == H - h0 + 1
+    net.close()
+    if ky * kx > 64:
+        assert [L["kind"] for L in ls][-2:] == [1, 0] and "+pool" not in ls[-3]["name"], ls
+
+
+@pytest.mark.parametrize("dt,cin,k,cout,p", [("bf16", 112, 2, 144, 17), ("bf16", 16, 1, 128, 12), ("f32", 16, 1, 16, 30),
+                                             ("bf16", 32, 1, 64, 17), ("f32", 1, 3, 48, 17)])
+def test_pool_windows_beyond_any_fused_tile(dt, cin, k, cout, p):
+    """Layers that fuse their pools by the work rule: a window of more outputs
+    than their largest tile is pooled by itself."""
+    layers = ([wl.conv(2, 3, cin)] if cin > 1 else []) + [wl.conv(k, cin, cout), wl.pool(p, cout), wl.fc(1, cout, 16),
+                                                          wl.fc(1, 16, 3, "softmax")]
+    h0, w0 = ix.patch_hw(layers)
+    net = _net(layers, dt)
+    ls = net.launches(2, h0 + 90, w0 + 71)
+    net.close()
+    assert sum(L["kind"] == 1 for L in ls) == 1, ls
+
+
+def test_tilings_that_do_not_fit_leave_no_error_message():
+    layers = [wl.conv(4, 1, 48), wl.conv(3, 48, 48), wl.pool(9, 48), wl.fc(2, 48, 200), wl.fc(1, 200, 2, "softmax")]
+    net = _net(layers)
+    with pytest.raises(fsb.FsError, match="smaller than the window"):
+        net.plan(1, 9, 60)
+    before = fsb.load().fs_last_error()
+    net.plan(1, 60, 60)
+    assert fsb.load().fs_last_error() == before
+    net.close()
