@@ -1607,11 +1607,13 @@ hipError_t launch_one(const ConvArgs &a, int gx, int gy, hipStream_t s)
     X(2, 1, 1, 1) X(2, 2, 1, 1) X(2, 3, 1, 1) X(2, 4, 1, 1) X(4, 1, 1, 1) X(4, 2, 1, 1)
 
 // Half-step instances (c_in a multiple of 16): float32 layers whose operands
-// are split into f16 pairs, and bf16 layers.
+// are split into f16 pairs, and bf16 layers.  Every channel tile goes down to
+// as few pixels as in the lists above, so no window that fits there is refused
+// here.
 #define FS_CONV_TILES_HS(X)                                                                     \
     X(1, 1, 1, 1) X(1, 2, 1, 1) X(1, 3, 1, 1) X(1, 4, 1, 1) X(2, 1, 1, 1) X(2, 2, 1, 1)          \
     X(2, 3, 1, 1) X(2, 4, 1, 1) X(4, 1, 1, 1) X(4, 2, 1, 1) X(4, 3, 1, 1) X(4, 4, 1, 1)          \
-    X(2, 3, 1, 2) X(4, 3, 1, 2) X(2, 7, 1, 1) X(4, 7, 1, 1) X(1, 7, 2, 1)          \
+    X(2, 3, 1, 2) X(4, 3, 1, 2) X(1, 7, 1, 1) X(2, 7, 1, 1) X(4, 7, 1, 1) X(1, 7, 2, 1)          \
     X(2, 7, 2, 1) X(4, 7, 2, 1) X(2, 4, 2, 1) X(4, 4, 2, 1)
 #define FS_CONV_TILES_RUN_HS(X) \
     X(2, 2, 1, 1) X(4, 2, 1, 1) X(4, 3, 1, 1) X(4, 3, 1, 2) X(4, 4, 1, 1) X(4, 7, 1, 1) X(4, 7, 2, 1)

@@ -47,3 +47,11 @@ def test_pools_beyond_a_fused_tile(fsb, dt, cin, cout, ky, kx):
     names = _check(fsb, layers, dt, (21, 30), ky + kx)
     if ky * kx > 64:
         assert any(n.startswith("pool_") for n in names), names
+
+
+@pytest.mark.parametrize("dt,cin,k,cout", [("f32", 192, 3, 100), ("f32", 256, 2, 112), ("f32", 240, 2, 97),
+                                           ("bf16", 336, 3, 112), ("bf16", 240, 5, 100)])
+def test_seven_channel_blocks_in_64_pixel_tiles(fsb, dt, cin, k, cout):
+    layers = [wl.conv(1, 3, cin), wl.fc(k, cin, cout), wl.fc(1, cout, 3, "softmax")]
+    names = _check(fsb, layers, dt, (40, 53), cin + k)
+    assert any("<1, 7, 1, 1, " in n and n.split(">")[0].endswith("true") for n in names), names

@@ -63,3 +63,42 @@ def test_tilings_that_do_not_fit_leave_no_error_message():
     net.plan(1, 60, 60)
     assert fsb.load().fs_last_error() == before
     net.close()
+
+
+@pytest.mark.parametrize("cin", [16, 48, 96, 128, 192, 256])
+@pytest.mark.parametrize("k", [1, 2, 3, 5])
+def test_half_steps_refuse_no_layer(monkeypatch, cin, k):
+    """Every float32 layer that plans on the float32 products plans on the
+    split ones too, whatever its outputs: the largest windows fit only in the
+    64-pixel tiles."""
+    taken = 0
+    for cout in (20, 48, 100, 112, 128, 200, 300):
+        layers = [wl.conv(1, 1, cin), wl.conv(k, cin, cout), wl.fc(1, cout, 2, "softmax")]
+        net = _net(layers)
+        for H, W in ((300, 300), (k + 60, k + 6)):
+            with monkeypatch.context() as m:
+                m.setenv("FRAGSCAN_SPLIT", "0")
+                try:
+                    net.plan(1, H, W)
+                except fsb.FsError:
+                    continue
+            half = [L["name"].split(">")[0].endswith("true") for L in net.launches(1, H, W)]
+            assert half[1], (cin, k, cout, H, W)
+            taken += 1
+        net.close()
+    assert taken or (cin, k) in ((192, 5), (256, 5))  # (no tile holds a 5x5 window of these)
+
+
+@pytest.mark.parametrize("dt,layers,H,W", [
+    ("f32", [wl.conv(2, 1, 16, kx=1), wl.conv(1, 16, 144), wl.fc(3, 144, 100), wl.fc(1, 100, 3, "softmax")], 504, 8),
+    ("f32", [wl.conv(1, 1, 192), wl.fc(3, 192, 100), wl.fc(1, 100, 2, "softmax")], 300, 300),
+    ("f32", [wl.conv(1, 1, 256), wl.fc(3, 256, 112), wl.fc(1, 112, 2, "softmax")], 300, 300),
+    ("bf16", [wl.conv(9, 1, 304), wl.pool(2, 304, kx=3), wl.fc(3, 304, 100), wl.fc(1, 100, 3, "softmax")], 74, 37),
+    ("bf16", [wl.conv(1, 1, 240), wl.fc(5, 240, 100), wl.fc(1, 100, 2, "softmax")], 300, 300),
+    ("bf16", [wl.conv(1, 1, 336), wl.fc(3, 336, 112), wl.fc(1, 112, 2, "softmax")], 300, 300)])
+def test_seven_channel_blocks_in_64_pixel_tiles(dt, layers, H, W):
+    """65 to 112 outputs behind windows that leave LDS for 64 pixels only."""
+    net = _net(layers, dt)
+    names = [L["name"] for L in net.launches(1, H, W)]
+    net.close()
+    assert any("<1, 7, 1, 1, " in n and n.split(">")[0].endswith("true") for n in names), names
