@@ -838,9 +838,8 @@ void small_grid_tile(const fs_net *net, int li, const Geo &in, int B, NetLayer &
 // c_in k^2 ov < elem * (peak FLOP/s / HBM bytes/s): every layer of the five
 // workloads except N4's 48 -> 48 convolutions, whose fused form measured
 // 10-35% slower.  FRAGSCAN_POOL_FUSE=1 / 0 forces it on / off.
-// small: small_grid_tile chose 64-pixel tiles; the separate pool's launch costs
-// more there than the recomputed halo (N4 on 103x110: 69 -> 55 us a scan, 128^2
-// 74 -> 61, 180^2, the last 4x4 only, 13.4 us either way).
+// small: small_grid_tile chose 64-pixel tiles; there the count of fused tiles
+// decides (small_grid_fusion).
 bool want_pool_fusion(const fs_net *net, int li, const NetLayer &l, bool small)
 {
     const int nl = (int)net->L.size();
@@ -853,6 +852,28 @@ bool want_pool_fusion(const fs_net *net, int li, const NetLayer &l, bool small)
     const double ov = (p.k == 2 && p.kx == 2) ? 0.35 : 0.5;
     const double ridge = net->dtype == DT_BF16 ? 2516.6e12 / 8e12 : 157.3e12 / 8e12;  // FLOP per byte
     return (double)l.cin * l.k * l.kx * ov < elem_of(net->dtype) * ridge;
+}
+
+// Whether a pool stays in the epilogue of a 64-pixel tile on a small grid,
+// given the fused tiles the planner found: fusing saves the pool's launch (and
+// for windows without a row-band kernel most of its time) and pays a halo that
+// grows with the window.  Up to one tile per CU it always paid; beyond, pools
+// the row-band kernel would run stay up to two per CU while the halo less than
+// doubles the tiles, the others up to four per CU.  Us a scan, separate / fused
+// (fused tiles), 48 -> 48 layers:
+//   3x3 + 2x2 28.6 / 25.1 (80), 33.1 / 28.9 (336); 3x3 + 3x3 33.3 / 29.1 (464);
+//   3x3 + 4x4 28.7 / 27.1 (144); 5x5 + 4x4 32.6 / 34.4 (328), 35.8 / 41.7 (632);
+//   3x3 + 5x5 36.9 / 29.0 (512), 48.2 / 38.2 (992); 5x5 + 5x5 45.9 / 48.1 (936);
+//   3x3 + 6x6 39.9 / 37.0 (872), 45.7 / 48.5 (1728); 3x3 + 8x8 46.6 / 63.9 (2968),
+//   54.1 / 220 (14520).
+bool small_grid_fusion(const fs_net *net, const NetLayer &p, const Geo &in, int B, const ConvArgs &a, int ky, int kx)
+{
+    if (const char *e = getenv("FRAGSCAN_POOL_FUSE"); e && e[0]) return true;  // forced
+    const long long ncu = net->ncu > 0 ? net->ncu : 256;
+    const long long tiles = (long long)B * in.Qy * in.Qx * a.nbands * a.tiles_per_band;
+    if (tiles <= ncu) return true;
+    if (!pool_has_row_bands(p.k, p.kx)) return tiles <= 4 * ncu;
+    return tiles <= 2 * ncu && tiles < 2 * count_tiles(in, ky, kx, B, a.mt, tiles);
 }
 
 // First output coordinate (along one axis) of the final fragments' axis
@@ -1045,6 +1066,7 @@ fs_status make_plan(const fs_net *net, int B, int H, int W, Plan &P, const View 
             // small grids, 128 to 512 elsewhere), or whose tile does not fit
             // in LDS: the pool runs by itself.
             if (pool_fuse && plan_tiles(true) != FS_OK) pool_fuse = false;
+            if (pool_fuse && small && !small_grid_fusion(net, net->L[li + 1], g, B, a, ky, kx)) pool_fuse = false;
             if (l.has_w32 && !fused_here && !pool_fuse && want_direct) {
                 L.direct = true;
                 L.conv.lds_bytes = 0;

@@ -209,6 +209,8 @@ struct HeadArgs {
 hipError_t launch_conv(const ConvArgs &a, int dtype, bool in_f32, int mb, int nb, int wn, int wk, bool vec, bool hs,
                        int grid_x, int grid_y, hipStream_t s);
 hipError_t launch_pool(const PoolArgs &a, int dtype, bool in_f32, int grid, hipStream_t s);
+// Whether the row-band pool kernel has the window (else one workgroup per child row).
+bool pool_has_row_bands(int ky, int kx);
 // Mirrored borders: out[B][He][We][C] from in[B][H][W][C], extended index
 // (y, x) reading image pixel (mirror(y - p0y, H), mirror(x - p0x, W)).
 enum BorderMode { BORDER_VALID = 0, BORDER_REFLECT = 1, BORDER_SYMMETRIC = 2 };

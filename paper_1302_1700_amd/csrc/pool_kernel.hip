@@ -319,6 +319,15 @@ hipError_t go_k(const PoolArgs &a, int grid, hipStream_t s)
 
 }  // namespace
 
+bool pool_has_row_bands(int ky, int kx)
+{
+#define FS_POOL_HAS(KY, KX) \
+    if (ky == KY && kx == KX) return true;
+    FS_POOL_ROWS(FS_POOL_HAS)
+#undef FS_POOL_HAS
+    return false;
+}
+
 hipError_t launch_pool(const PoolArgs &a, int dtype, bool in_f32, int grid, hipStream_t s)
 {
     if (dtype == DT_F32) return (a.C % 4 == 0) ? go_k<false, false, 4>(a, grid, s) : go_k<false, false, 1>(a, grid, s);

@@ -102,3 +102,21 @@ def test_seven_channel_blocks_in_64_pixel_tiles(dt, layers, H, W):
     names = [L["name"] for L in net.launches(1, H, W)]
     net.close()
     assert any("<1, 7, 1, 1, " in n and n.split(">")[0].endswith("true") for n in names), names
+
+
+@pytest.mark.parametrize("p,side,fused", [(2, 60, True), (2, 130, True), (3, 130, True), (4, 64, True), (4, 130, False),
+                                          (5, 96, True), (6, 96, True), (6, 130, False), (7, 130, False),
+                                          (8, 60, False), (8, 130, False)])
+def test_small_grid_pools_by_fused_tiles(monkeypatch, p, side, fused):
+    """A pool behind a 64-pixel tile is fused while the fused grid stays near
+    one round of workgroups: never the thousands of one-value tiles of a wide
+    window (8x8 on 130^2: 14520)."""
+    layers = [wl.conv(3, 1, 48), wl.conv(3, 48, 48), wl.pool(p, 48), wl.fc(2, 48, 200), wl.fc(1, 200, 2, "softmax")]
+    net = _net(layers)
+    mid = [L for L in net.launches(1, side, side + 3) if L["layer"] == 1]
+    assert len(mid) == 1 and mid[0]["name"].startswith("conv_frag_mfma<2, 3, 1, 2, "), mid
+    assert ("+pool" in mid[0]["name"]) == fused, mid
+    assert mid[0]["grid"] <= 1024, mid
+    monkeypatch.setenv("FRAGSCAN_POOL_FUSE", "1")
+    assert "+pool" in [L for L in net.launches(1, side, side + 3) if L["layer"] == 1][0]["name"]
+    net.close()
