@@ -120,3 +120,21 @@ def test_small_grid_pools_by_fused_tiles(monkeypatch, p, side, fused):
     monkeypatch.setenv("FRAGSCAN_POOL_FUSE", "1")
     assert "+pool" in [L for L in net.launches(1, side, side + 3) if L["layer"] == 1][0]["name"]
     net.close()
+
+
+@pytest.mark.parametrize("cin,cout,p,px,side,fused", [
+    (16, 80, 2, 2, 300, True), (16, 224, 3, 3, 300, True), (48, 128, 4, 4, 300, False), (48, 128, 2, 3, 300, False),
+    (48, 100, 2, 2, 300, False), (48, 100, 8, 8, 300, False), (80, 112, 5, 5, 300, True), (80, 112, 5, 5, 90, False),
+    (80, 112, 8, 8, 300, True), (16, 224, 10, 10, 300, False), (48, 128, 10, 10, 90, False), (16, 64, 4, 4, 300, True)])
+def test_wide_half_step_pools(monkeypatch, cin, cout, p, px, side, fused):
+    """bf16 half-step layers of more than 64 outputs (a separate pool before
+    they took the vector path) fuse only the pools that run faster so; up to
+    64 outputs the work rule alone decides."""
+    layers = [wl.conv(3, 1, cin), wl.conv(2, cin, cout), wl.pool(p, cout, kx=px), wl.fc(1, cout, 16),
+              wl.fc(1, 16, 2, "softmax")]
+    net = _net(layers, "bf16")
+    mid = lambda: [L for L in net.launches(1, side, side + 3) if L["layer"] == 1][0]["name"]
+    assert ("+pool" in mid()) == fused, mid()
+    monkeypatch.setenv("FRAGSCAN_POOL_FUSE", "1")
+    assert "+pool" in mid()
+    net.close()
