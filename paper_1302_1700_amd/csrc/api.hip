@@ -866,14 +866,14 @@ bool want_pool_fusion(const fs_net *net, int li, const NetLayer &l, bool small)
 //   3x3 + 5x5 36.9 / 29.0 (512), 48.2 / 38.2 (992); 5x5 + 5x5 45.9 / 48.1 (936);
 //   3x3 + 6x6 39.9 / 37.0 (872), 45.7 / 48.5 (1728); 3x3 + 8x8 46.6 / 63.9 (2968),
 //   54.1 / 220 (14520).
-bool small_grid_fusion(const fs_net *net, const NetLayer &p, const Geo &in, int B, const ConvArgs &a, int ky, int kx)
+bool small_grid_fusion(const fs_net *net, const NetLayer &l, const NetLayer &p, const Geo &in, int B, int mt,
+                       long long tiles)
 {
     if (const char *e = getenv("FRAGSCAN_POOL_FUSE"); e && e[0]) return true;  // forced
     const long long ncu = net->ncu > 0 ? net->ncu : 256;
-    const long long tiles = (long long)B * in.Qy * in.Qx * a.nbands * a.tiles_per_band;
     if (tiles <= ncu) return true;
     if (!pool_has_row_bands(p.k, p.kx)) return tiles <= 4 * ncu;
-    return tiles <= 2 * ncu && tiles < 2 * count_tiles(in, ky, kx, B, a.mt, tiles);
+    return tiles <= 2 * ncu && tiles < 2 * count_tiles(in, l.k, l.kx, B, mt, tiles);
 }
 
 // Whether a pool goes into the epilogue of a bf16 half-step layer of more than
@@ -888,14 +888,14 @@ bool small_grid_fusion(const fs_net *net, const NetLayer &p, const Geo &in, int 
 //   80 -> 112 2x2, 800^2: 5x5 603 / 249, 8x8 1380 / 514 (4), 10x10 2005 / 1237 (15.7);
 //   ... 90^2: 5x5 20.1 / 25.1, 6x6 22.0 / 26.3 (64 and 72 tiles);
 //   48 -> 128 3x3, 300^2: 6x6 96 / 98 (7.9), 8x8 175 / 175 (13.6), 10x10 204 / 464 (39.6).
-bool wide_half_fusion(const fs_net *net, const NetLayer &l, const NetLayer &p, const Geo &in, int B, const ConvArgs &a)
+bool wide_half_fusion(const fs_net *net, const NetLayer &l, const NetLayer &p, const Geo &in, int B, int mt,
+                      long long tiles)
 {
     if (const char *e = getenv("FRAGSCAN_POOL_FUSE"); e && e[0]) return true;  // forced
     if (l.cout % 8) return false;
     if (pool_has_row_bands(p.k, p.kx)) return p.k == p.kx && p.k <= 3;
     const long long ncu = net->ncu > 0 ? net->ncu : 256;
-    const long long tiles = (long long)B * in.Qy * in.Qx * a.nbands * a.tiles_per_band;
-    return 2 * tiles >= ncu && tiles <= 16 * count_tiles(in, l.k, l.kx, B, a.mt, tiles);
+    return 2 * tiles >= ncu && tiles <= 16 * count_tiles(in, l.k, l.kx, B, mt, tiles);
 }
 
 // First output coordinate (along one axis) of the final fragments' axis
@@ -1084,13 +1084,23 @@ fs_status make_plan(const fs_net *net, int B, int H, int W, Plan &P, const View 
                 }
                 return st;
             };
+            const long long ncu = net->ncu > 0 ? net->ncu : 256;
+            auto fused_tiles = [&] { return (long long)B * F * a.nbands * a.tiles_per_band; };
+            // A small grid's tile of 129 to 224 outputs was chosen by its
+            // tiles without the pool's halo: a tile of fewer pixels only
+            // while the fused ones stay within two (32 pixels) or four (64)
+            // per CU.  Us, that tile / the layer's own (fused tiles):
+            //   16 -> 176 2x2 + 2x2 7.7 / 11.7 (160), + 4x4 27.6 / 40.6 (632), + 5x5 33.6 / 41.0 (968);
+            //   48 -> 200 1x1 + 3x3 14.2 / 11.9 (648), + 5x5 57.4 / 22.8 (3656), + 8x8 291 / 122 (14520).
+            if (pool_fuse && !small)
+                while (l.mb && (plan_tiles(true) != FS_OK || fused_tiles() > 2 * l.mb * ncu)) l.mb = l.mb == 1 ? 2 : 0;
             // A pool window of more outputs than any tile holds (64 on the
             // small grids, 128 to 512 elsewhere), or whose tile does not fit
             // in LDS: the pool runs by itself.
             if (pool_fuse && plan_tiles(true) != FS_OK) pool_fuse = false;
-            if (pool_fuse && small && !small_grid_fusion(net, net->L[li + 1], g, B, a, ky, kx)) pool_fuse = false;
+            if (pool_fuse && small && !small_grid_fusion(net, l, net->L[li + 1], g, B, a.mt, fused_tiles())) pool_fuse = false;
             if (pool_fuse && net->dtype == DT_BF16 && l.hs && a.nbu > 4 &&
-                !wide_half_fusion(net, l, net->L[li + 1], g, B, a))
+                !wide_half_fusion(net, l, net->L[li + 1], g, B, a.mt, fused_tiles()))
                 pool_fuse = false;
             if (l.has_w32 && !fused_here && !pool_fuse && want_direct) {
                 L.direct = true;

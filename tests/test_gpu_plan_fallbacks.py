@@ -55,3 +55,12 @@ def test_seven_channel_blocks_in_64_pixel_tiles(fsb, dt, cin, k, cout):
     layers = [wl.conv(1, 3, cin), wl.fc(k, cin, cout), wl.fc(1, cout, 3, "softmax")]
     names = _check(fsb, layers, dt, (40, 53), cin + k)
     assert any("<1, 7, 1, 1, " in n and n.split(">")[0].endswith("true") for n in names), names
+
+
+@pytest.mark.parametrize("cin,cout,p,more", [(16, 176, 3, (60, 51)), (48, 200, 5, (70, 61)), (16, 144, 8, (90, 97)),
+                                             (32, 129, 10, (12, 15))])
+def test_wide_layers_with_pools_on_small_grids(fsb, cin, cout, p, more):
+    """Every tile size the planner may take there."""
+    layers = [wl.conv(2, 1, cin), wl.conv(1, cin, cout), wl.pool(p, cout), wl.fc(1, cout, 20), wl.fc(1, 20, 3, "softmax")]
+    names = _check(fsb, layers, "f32", more, p)
+    assert any(", 7, 2, 1, " in n and "+pool" in n for n in names), names

@@ -138,3 +138,22 @@ def test_wide_half_step_pools(monkeypatch, cin, cout, p, px, side, fused):
     monkeypatch.setenv("FRAGSCAN_POOL_FUSE", "1")
     assert "+pool" in mid()
     net.close()
+
+
+@pytest.mark.parametrize("cin,k,cout", [(16, 2, 176), (48, 1, 200)])
+@pytest.mark.parametrize("p,side", [(2, 60), (3, 90), (5, 90), (5, 128), (8, 30), (8, 128), (10, 30)])
+def test_small_grid_pools_of_wide_layers(monkeypatch, cin, k, cout, p, side):
+    """129 to 224 outputs on a small grid: the pool stays fused, in the small
+    tile only while its halo leaves the tiles near a round of workgroups."""
+    layers = [wl.conv(3, 1, cin), wl.conv(k, cin, cout), wl.pool(p, cout), wl.fc(1, cout, 16),
+              wl.fc(1, 16, 2, "softmax")]
+    net = _net(layers)
+    mid = lambda: [L for L in net.launches(1, side, side + 3) if L["layer"] == 1][0]
+    got = mid()
+    assert "+pool" in got["name"], got
+    mb = int(got["name"].split("<")[1].split(",")[0])
+    assert got["grid"] <= {1: 512, 2: 1024, 4: 1 << 24}[mb], got
+    assert mb == {(2, 60): 1, (8, 30): 2, (8, 128): 4, (10, 30): 4}.get((p, side), mb), got
+    monkeypatch.setenv("FRAGSCAN_RUN", "0")  # keeps the layer's own tile
+    assert mid()["name"].startswith("conv_frag_mfma<4, 7, 2, 1, ")
+    net.close()
