@@ -1157,9 +1157,14 @@ fs_status make_plan(const fs_net *net, int B, int H, int W, Plan &P, const View 
                     // pad its LDS to admit one.  Other tiles and the f16
                     // products are faster at two (N4 mirrored 512x512,
                     // split: 122 against 172 us; 16 -> 100 channels, 7 x 1,
-                    // 701x903: 89 against 106).
-                    if (fused_here && !L.hs && L.nb == 7 && L.wn == 2 && net->ncu > 0 &&
-                        (long long)gx * L.gy <= 12LL * net->ncu &&
+                    // 701x903: 89 against 106), except where the tiles that
+                    // hold pixels are no more than the CUs: two on one CU
+                    // leave another idle (900 fragments of one pixel or none,
+                    // 208 -> 100: 32 against 59 us; dense grids of a tile per
+                    // CU 0-5% faster).
+                    const bool own_tile = !L.hs && L.nb == 7 && L.wn == 2 && (long long)gx * L.gy <= 12LL * net->ncu;
+                    if (fused_here && net->ncu > 0 &&
+                        (own_tile || count_tiles(g, ky, kx, B, a.mt, net->ncu) <= net->ncu) &&
                         conv_blocks_per_cu(net->dtype, g.is_image, L.mb, L.nb, L.wn, L.wk, L.vec, L.hs, run, lds) == 2)
                         lds = std::max(lds, (int)(kMaxLdsBytes / 2 + 1024));
                     // plan-only nets: 256 CUs, one workgroup each

@@ -64,3 +64,16 @@ def test_wide_layers_with_pools_on_small_grids(fsb, cin, cout, p, more):
     layers = [wl.conv(2, 1, cin), wl.conv(1, cin, cout), wl.pool(p, cout), wl.fc(1, cout, 20), wl.fc(1, 20, 3, "softmax")]
     names = _check(fsb, layers, "f32", more, p)
     assert any(", 7, 2, 1, " in n and "+pool" in n for n in names), names
+
+
+def test_sparse_head_grids_take_a_cu_each(fsb):
+    """A fused head whose tiles that hold pixels are no more than the CUs runs
+    one workgroup per CU, on larger grids as many as fit."""
+    layers = [wl.conv(4, 1, 32), wl.pool(8, 32, stride=5), wl.pool(2, 32), wl.conv(4, 32, 208), wl.pool(3, 208),
+              wl.fc(1, 208, 100), wl.fc(1, 100, 2, "none")]
+    params = wl.make_weights(layers, 7, 0.05)
+    net = fsb.Net(layers, params, 1)
+    sparse, dense = net.launches(1, net.patch + 8, net.patch + 11)[-1], net.launches(4, 400, 400)[-1]
+    net.close()
+    assert sparse["name"] == dense["name"] and "+head" in sparse["name"], (sparse, dense)
+    assert (sparse["per_cu"], dense["per_cu"]) == (1, 2), (sparse, dense)
