@@ -1422,17 +1422,26 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
                 dtm.qr(p, r, c);
                 const TC *src = tile + __mul24(__mul24(r, ew) + c, TS) + ch;
                 TC m = src[0];
-                for (int i = 0; i < kpy; ++i)
-                    for (int j = 0; j < kpx; ++j) {
-                        const TC x = src[__mul24(__mul24(i, ew) + j, TS)];
-                        if constexpr (KEYS)
-                            m = (TC)max_i16x2(m, x);  // keys in the low half
-                        else if constexpr (BF)
-                            m = (TC)max_bf16x2_bounded(m, x);
-                        else
-                            m = fmaxf(m, x);
+                if constexpr (BF) {
+                    // two window pixels at a time, one in each half (two loads
+                    // in flight; 32 -> 100 + 8x8 pool: 259 -> 159 us)
+                    auto max2 = [](uint32_t x, uint32_t y) {
+                        return KEYS ? max_i16x2(x, y) : max_bf16x2_bounded(x, y);
+                    };
+                    uint32_t m2 = m * 0x10001u;
+                    for (int i = 0; i < kpy; ++i) {
+                        const TC *row = src + __mul24(__mul24(i, ew), TS);
+                        int j = 0;
+                        for (; j + 1 < kpx; j += 2)
+                            m2 = max2(m2, row[__mul24(j, TS)] | (uint32_t)row[__mul24(j + 1, TS)] << 16);
+                        if (j < kpx) m2 = max2(m2, row[__mul24(j, TS)] * 0x10001u);
                     }
-                if constexpr (KEYS) m = (TC)bf16x2_key(m);
+                    m2 = max2(m2, m2 >> 16);
+                    m = (TC)(KEYS ? bf16x2_key(m2) : m2);
+                } else {
+                    for (int i = 0; i < kpy; ++i)
+                        for (int j = 0; j < kpx; ++j) m = fmaxf(m, src[__mul24(__mul24(i, ew) + j, TS)]);
+                }
                 if (child_ok(r, c)) child_ptr(r, c)[ch] = m;
             }
         }

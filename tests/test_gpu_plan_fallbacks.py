@@ -77,3 +77,26 @@ def test_sparse_head_grids_take_a_cu_each(fsb):
     net.close()
     assert sparse["name"] == dense["name"] and "+head" in sparse["name"], (sparse, dense)
     assert (sparse["per_cu"], dense["per_cu"]) == (1, 2), (sparse, dense)
+
+
+@pytest.mark.parametrize("act", ["tanh", "none"])
+@pytest.mark.parametrize("cout,ky,kx", [(20, 2, 2), (33, 3, 3), (100, 5, 5), (100, 4, 3), (100, 2, 5), (39, 1, 4), (17, 3, 1)])
+def test_fused_pools_of_odd_channel_counts(fsb, monkeypatch, act, cout, ky, kx):
+    """bf16 outputs not in whole 16-byte chunks, even and odd window columns:
+    the fused pool's values are the separate one's bit for bit."""
+    layers = [wl.conv(2, 3, 32), wl.conv(2, 32, cout, act), wl.pool(ky, cout, kx=kx), wl.fc(1, cout, 16),
+              wl.fc(1, 16, 3, "none")]
+    h0, w0 = ix.patch_hw(layers)
+    params = wl.make_weights(layers, cout, 0.1)
+    img = torch.from_numpy(wl.make_image(cout + 1, 2, h0 + 37, w0 + 50, 3)).cuda()
+    got = {}
+    for fuse in ("1", "0"):
+        monkeypatch.setenv("FRAGSCAN_POOL_FUSE", fuse)
+        net = fsb.Net(layers, params, 3, 0, "bf16")
+        names = [L["name"] for L in net.launches(*img.shape[:3])]
+        print("odd channels", act, cout, (ky, kx), names, flush=True)
+        assert ("+pool" in names[1]) == (fuse == "1"), names
+        got[fuse] = net.scan(img).clone()
+        torch.cuda.synchronize()
+        net.close()
+    assert torch.equal(got["1"], got["0"])
