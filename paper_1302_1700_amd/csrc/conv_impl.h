@@ -948,7 +948,8 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
                     wnx += s + t + WD < last ? wstep_h : 0;
                 }
         };
-        if constexpr (WN == 2 && WK == 1 && NB >= 2) {
+        // (as in the plain walk below; paired bf16 blocks both hold channels)
+        if constexpr (!(BF && NB % 2 == 0) && WN == 2 && WK == 1 && NB >= 2) {
             if (nb0 + NB - 1 >= a.nbu)
                 kwalk(std::integral_constant<int, NB - 1>());
             else

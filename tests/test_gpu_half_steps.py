@@ -248,3 +248,21 @@ def test_nan_pixels_lose_in_every_pool(fsb, monkeypatch, net):
     assert 0 < masks["f32", "0"].sum() < masks["f32", "0"].size
     for k, m in masks.items():
         assert np.array_equal(m, masks["f32", "0"]), (k, m.sum(), masks["f32", "0"].sum())
+
+
+@pytest.mark.parametrize("cout", [97, 112, 48])
+@pytest.mark.parametrize("mb", [2, 4])
+def test_bf16_padding_blocks_of_paired_tiles(fsb, monkeypatch, cout, mb):
+    """A forced 4 x 2 channel tile whose last block is past an odd count of
+    output blocks: in a pair of bf16 blocks that block still holds channels
+    (8g + 4 .. 8g + 7 of the pair's 32), and none may be dropped."""
+    layers = [wl.conv(2, 3, 48), wl.conv(2, 48, cout), wl.conv(1, cout, 16), wl.fc(1, 16, 3, "none")]
+    w0 = ix.patch_size(layers)
+    params = wl.make_weights(layers, cout, 0.1)
+    img = wl.make_image(cout + 1, 1, w0 + 33, w0 + 40, 3)
+    base, _ = _scan(fsb, layers, params, img, "bf16")
+    monkeypatch.setenv("FRAGSCAN_TILE", "1:%d,4,2" % mb)
+    got, names = _scan(fsb, layers, params, img, "bf16")
+    print("paired tiles", cout, mb, names, flush=True)
+    assert names[1].startswith("conv_frag_mfma<%d, 4, 2, 1, " % mb) and _half(names[1]), names
+    assert np.array_equal(got, base)
