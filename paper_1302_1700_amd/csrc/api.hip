@@ -549,8 +549,7 @@ void plan_run_tiles(const NetLayer &l, const Geo &in, int mt, int cs, int es, in
 // hands the blocks it does not finish to their owners.
 size_t split_k_lds(int mb, int nb, int wk)
 {
-    const int me = (mb + wk - 1) / wk;
-    return (size_t)wk * (wk - 1) * (4 / wk) * me * nb * 64 * 16;
+    return (size_t)(wk - 1) * (4 / wk) * mb * nb * 64 * 16;
 }
 
 // Tile choice for a conv launch (the tiling itself is described in conv_impl.h).

@@ -1124,12 +1124,11 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
 
     // ---- split-K reduction ----------------------------------------------------
     // The waves of a K split share the finish: wave wk adds up and owns pixel
-    // blocks wk*ME .. of the wave tile (with fewer blocks than waves the last
-    // waves own none), each partial sum read once from LDS, summed in the
-    // order of the K parts.
-    constexpr int ME = (MB + WK - 1) / WK;  // pixel blocks a wave finishes
-    const int mb0 = wm * MB + wk * ME;      // ... from block mb0 of the tile on
-    const bool own = wk * ME < MB;
+    // blocks wk*ME .. of the wave tile, each partial sum read once from LDS,
+    // summed in the order of the K parts.
+    static_assert(MB % WK == 0, "the waves of a K split finish equal shares of the pixel blocks");
+    constexpr int ME = MB / WK;         // pixel blocks a wave finishes
+    const int mb0 = wm * MB + wk * ME;  // ... from block mb0 of the tile on
     f4 fin[WK > 1 ? ME : 1][WK > 1 ? NB : 1];
     f4(&eacc)[ME][NB] = [&]() -> f4(&)[ME][NB] {
         if constexpr (WK > 1) return fin; else return acc;
@@ -1143,16 +1142,16 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
         __syncthreads();  // the window is no longer read
 #pragma unroll
         for (int d = 0; d < WK; ++d)
-            if (d != wk && d * ME < MB) {
+            if (d != wk) {
 #pragma unroll
                 for (int i = 0; i < ME; ++i)
 #pragma unroll
-                    for (int j = 0; j < NB; ++j) *slot(d, wk, i, j) = acc[(d * ME + i) % MB][j];
+                    for (int j = 0; j < NB; ++j) *slot(d, wk, i, j) = acc[d * ME + i][j];
             }
         __syncthreads();
 #pragma unroll
         for (int d = 0; d < WK; ++d)
-            if (d == wk && d * ME < MB) {
+            if (d == wk) {
 #pragma unroll
                 for (int i = 0; i < ME; ++i)
 #pragma unroll
@@ -1160,7 +1159,7 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
                         f4 t = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                         for (int w = 0; w < WK; ++w) {
-                            const f4 v = w == d ? acc[(d * ME + i) % MB][j] : *slot(d, w, i, j);
+                            const f4 v = w == d ? acc[d * ME + i][j] : *slot(d, w, i, j);
                             t = w == 0 ? v : t + v;
                         }
                         fin[i][j] = t;
@@ -1183,7 +1182,7 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
     if (a.head_ncls > 0) {
         float *red = reinterpret_cast<float *>(smem);
         __syncthreads();  // the LDS window / partial sums (which red reuses) are no longer read
-        if (own) fused_head_partials<ME, NB, WN, BF, SPLIT>(a, eacc, nb0, mb0, wn, lm, g, red);
+        fused_head_partials<ME, NB, WN, BF, SPLIT>(a, eacc, nb0, mb0, wn, lm, g, red);
         __syncthreads();
         fused_head_finish<WN>(
             a, img, npix,
@@ -1234,7 +1233,6 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
     constexpr int TS = NW + TPAD;
     // keys: bf16 runs are written as order keys (bf16x2_key), for the pool
     auto stage_tile = [&](TC *tile, bool keys) {
-        if (!own) return;
 #pragma unroll
         for (int i = 0; i < ME; ++i) {
             TC *row = tile + ((mb0 + i) * 16 + lm) * TS;
@@ -1490,7 +1488,6 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
     }
 
     // Direct: every lane writes its runs straight from registers.
-    if (!own) return;
     const size_t osz = (size_t)a.out_h * a.out_w * a.cout;
     TC *outp = reinterpret_cast<TC *>(a.out) + (size_t)q * osz;
     TC *outp1 = reinterpret_cast<TC *>(a.out) + (size_t)q1 * osz;
