@@ -160,33 +160,28 @@ int dbg_shrink_at()
 }
 
 // float -> f16 bits, round to nearest even, for |f| < 65504 (values of the
-// split weights); f16 bits -> float.
+// split weights); f16 bits -> float.  (Both ways are computed and one taken:
+// loops over these are vectorised.)
 uint16_t host_f2h(float f)
 {
-    uint32_t u;
+    uint32_t u, d;
     std::memcpy(&u, &f, 4);
-    const uint16_t sign = (uint16_t)((u >> 16) & 0x8000u);
+    const uint32_t sign = (u >> 16) & 0x8000u;
     u &= 0x7fffffffu;
-    if (u >= 0x38800000u)  // 2^-14 and up: rebias the exponent, round 13 bits off
-        return (uint16_t)(sign | ((u - 0x38000000u + 0xfffu + ((u >> 13) & 1u)) >> 13));
+    // 2^-14 and up: rebias the exponent, round 13 bits off
+    const uint32_t n = (u - 0x38000000u + 0xfffu + ((u >> 13) & 1u)) >> 13;
     // below: multiples of 2^-24, the spacing of floats in [0.5, 1)
-    float a;
-    std::memcpy(&a, &u, 4);
-    a += 0.5f;
-    std::memcpy(&u, &a, 4);
-    return (uint16_t)(sign | (u - 0x3f000000u));
+    const float a = std::fabs(f) + 0.5f;
+    std::memcpy(&d, &a, 4);
+    return (uint16_t)(sign | (u >= 0x38800000u ? n : d - 0x3f000000u));
 }
 
 float host_h2f(uint16_t h)
 {
-    const uint32_t m = h & 0x7fffu;
-    float f;
-    if (m >= 0x400u) {
-        const uint32_t u = (m << 13) + 0x38000000u;
-        std::memcpy(&f, &u, 4);
-    } else {
-        f = (float)m * 0x1p-24f;
-    }
+    const uint32_t m = h & 0x7fffu, u = (m << 13) + 0x38000000u;
+    float n;
+    std::memcpy(&n, &u, 4);
+    const float f = m >= 0x400u ? n : (float)(int)m * 0x1p-24f;
     return (h & 0x8000u) ? -f : f;
 }
 
@@ -290,31 +285,36 @@ void half_step_k(const NetLayer &l, int s, int g, int e, int &tap, int &ci)
 // f16 and lo = the nearest f16 of the rest keep 23 significand bits of every
 // weight within 2^-16 of the largest.  unscale takes scale and the inputs'
 // scale in_scale back off the sums.  False (layer stays float32) when a value
-// is not finite or a channel's range does not fit.
-bool pack_split_weights(const NetLayer &l, const float *w, const float *bias, float in_scale,
-                        std::vector<uint16_t> &out, std::vector<float> &bs, std::vector<float> &us)
+// is not finite or a channel's range does not fit.  out: zeroed, split_bytes.
+size_t split_bytes(const NetLayer &l) { return (size_t)l.ksteps_h * l.nbt * 2 * 64 * 16; }
+
+bool pack_split_weights(const NetLayer &l, const float *w, const float *bias, float in_scale, uint16_t *out,
+                        std::vector<float> &bs, std::vector<float> &us)
 {
-    const size_t K = (size_t)l.cin * l.k * l.kx;
+    const int taps = l.k * l.kx;
+    const size_t K = (size_t)l.cin * taps;
     bs.assign((size_t)l.nbt * 16, 0.f);
     us.assign((size_t)l.nbt * 16, 1.f);
-    const int taps = l.k * l.kx;
-    out.assign((size_t)l.ksteps_h * l.nbt * 2 * 64 * 8, 0);
-    std::vector<std::pair<int, int>> at((size_t)l.ksteps_h * 32);  // (weight index, packed index) of K index k
-    for (int s = 0, n = 0; s < l.ksteps_h; ++s)
+    std::vector<size_t> from((size_t)l.ksteps_h * 32);  // a channel's weight at each K index (K: none, zero)
+    for (int s = 0; s < l.ksteps_h; ++s)
         for (int g = 0; g < 4; ++g)
             for (int e = 0; e < 8; ++e) {
                 int tap, ci;
                 half_step_k(l, s, g, e, tap, ci);
-                at[n++] = {tap < taps ? ci * taps + tap : -1, (s * l.nbt * 128 + g * 16) * 8 + e};
+                from[((size_t)s * 4 + g) * 8 + e] = tap < taps ? (size_t)ci * taps + tap : K;
             }
+    std::vector<uint16_t> hi(K + 1, 0), lo(K + 1, 0);  // one channel's weights, in their own order
     for (int co = 0; co < l.cout; ++co) {
         const float *wc = w + co * K;
-        float m = 0.f;
+        int32_t mbits = 0;  // largest magnitude, as bits (not finite: 0x7f800000 and up)
         for (size_t i = 0; i < K; ++i) {
-            const float a = std::fabs(wc[i]);
-            if (!(a <= 3.4e38f)) return false;
-            m = std::max(m, a);
+            int32_t u;
+            std::memcpy(&u, wc + i, 4);
+            mbits = std::max(mbits, u & 0x7fffffff);
         }
+        float m;
+        std::memcpy(&m, &mbits, 4);
+        if (!(m <= 3.4e38f)) return false;
         int e = 0;
         if (m > 0.f) (void)std::frexp(m, &e);  // m in [2^(e-1), 2^e)
         if (e < -60 || e > 60) return false;
@@ -322,23 +322,33 @@ bool pack_split_weights(const NetLayer &l, const float *w, const float *bias, fl
         us[co] = 1.f / (scale * in_scale);
         bs[co] = bias[co] * scale * in_scale;
         if (!(std::fabs(bs[co]) <= 1e36f)) return false;
-        uint16_t *dst = out.data() + ((size_t)(co / 16) * 128 + co % 16) * 8;
-        for (const auto &[from, to] : at) {
-            if (from < 0) continue;
-            const float v = wc[from] * scale;
-            const uint16_t hi = host_f2h(v);
-            dst[to] = hi;
-            dst[to + 64 * 8] = host_f2h(v - host_h2f(hi));
+        for (size_t i = 0; i < K; ++i) {
+            const float v = wc[i] * scale;
+            const uint16_t h = host_f2h(v);
+            hi[i] = h;
+            lo[i] = host_f2h(v - host_h2f(h));
         }
+        uint16_t *dst = out + ((size_t)(co / 16) * 128 + co % 16) * 8;
+        const size_t *f = from.data();
+        for (int s = 0; s < l.ksteps_h; ++s)
+            for (int g = 0; g < 4; ++g, f += 8) {
+                uint16_t *d = dst + ((size_t)s * l.nbt * 128 + g * 16) * 8;
+                for (int q = 0; q < 8; ++q) {
+                    d[q] = hi[f[q]];
+                    d[q + 64 * 8] = lo[f[q]];
+                }
+            }
     }
     return true;
 }
 
-void pack_conv_weights(const NetLayer &l, const float *w, int dtype, std::vector<uint8_t> &out)
+// Weights in the order the K walk loads them: [step][block][64 lanes][16
+// bytes].  out: zeroed, weight_bytes.
+size_t weight_bytes(const NetLayer &l) { return (size_t)l.ksteps * l.nbt * 64 * 16; }
+
+void pack_conv_weights(const NetLayer &l, const float *w, int dtype, uint8_t *out)
 {
-    const int KSTEP = kstep_of(dtype), LPE = KSTEP / 4, es = elem_of(dtype);
-    const size_t n = (size_t)l.ksteps * l.nbt * 64 * LPE;
-    out.assign(n * es, 0);
+    const int KSTEP = kstep_of(dtype), LPE = KSTEP / 4;
     const int taps = l.k * l.kx;
     const size_t K = (size_t)l.cin * taps;
     std::vector<int> chan(l.nbt * 16);
@@ -1738,9 +1748,25 @@ static fs_status net_create(const fs_layer *layers, int32_t n_layers, int32_t in
 
     // --- pack parameters into one device block ---
     std::vector<uint8_t> blob;
-    auto push = [&](const void *p, size_t n) {
+    {
+        // room for all of it (weights of float32 layers in both packings, over
+        // 64 channels padded to tiles of up to 14 blocks): growing the block
+        // layer by layer copied it each time (N4: 1.74 -> 0.72 ms a net with
+        // that and the split's conversions vectorised)
+        size_t room = 1 << 18;
+        for (const NetLayer &l : L)
+            if (l.kind != FS_MAXPOOL)
+                room += ((size_t)l.cin * l.k * l.kx + 32) * (align_up(l.cout, 16) + (l.cout > 64 ? 208 : 0)) *
+                        (dtype == FS_F32 ? 8 : 2);
+        blob.reserve(room);
+    }
+    auto grow = [&](size_t n) {  // n zeroed bytes
         const size_t off = align_up(blob.size(), 256);
         blob.resize(off + n);
+        return off;
+    };
+    auto push = [&](const void *p, size_t n) {
+        const size_t off = grow(n);
         std::memcpy(blob.data() + off, p, n);
         return off;
     };
@@ -1817,9 +1843,8 @@ static fs_status net_create(const fs_layer *layers, int32_t n_layers, int32_t in
             delete net;
             return fail(FS_ERR_UNSUPPORTED, "layer %d: %d K steps cannot be split over %d waves", i, l.ksteps, l.wk);
         }
-        std::vector<uint8_t> pw;
-        pack_conv_weights(l, s.weight, dtype, pw);
-        l.w_off = push(pw.data(), pw.size());
+        l.w_off = grow(weight_bytes(l));
+        pack_conv_weights(l, s.weight, dtype, blob.data() + l.w_off);
         // bias in (block, row) order
         std::vector<float> bp((size_t)l.nbt * 16, 0.f);
         for (int r = 0; r < l.nbt * 16; ++r) {
@@ -1841,12 +1866,15 @@ static fs_status net_create(const fs_layer *layers, int32_t n_layers, int32_t in
         const char *sp = getenv("FRAGSCAN_SPLIT");
         const bool want_split = sp && sp[0] ? sp[0] == '1' : L.back().act == FS_ACT_SOFTMAX;
         if (dtype == FS_F32 && want_split && prev >= 0 && L[prev].act == FS_ACT_TANH && l.cin % 16 == 0 && l.cin <= 256) {
-            std::vector<uint16_t> wsp;
             std::vector<float> bs, us;
             l.ksteps_h = (l.k * l.kx * (l.cin / 16) + 1) / 2;
-            if (pack_split_weights(l, s.weight, bias.data(), kSplitInScale, wsp, bs, us)) {
-                l.hs = true;
-                l.ws_off = push(wsp.data(), wsp.size() * 2);
+            const size_t end = blob.size();
+            l.ws_off = grow(split_bytes(l));
+            l.hs = pack_split_weights(l, s.weight, bias.data(), kSplitInScale,
+                                      reinterpret_cast<uint16_t *>(blob.data() + l.ws_off), bs, us);
+            if (!l.hs) {
+                blob.resize(end);
+            } else {
                 l.bs_off = push(bs.data(), bs.size() * 4);
                 l.us_off = push(us.data(), us.size() * 4);
             }
