@@ -41,7 +41,7 @@ __device__ __forceinline__ uint16_t f2bf(float f)
 
 // V = elements per thread per access (4 x f32 or 8 x bf16 = 16 bytes; 1 = scalar)
 template <bool BF, bool IN_F32, int V>
-__global__ __launch_bounds__(256) void pool_frag(PoolArgs a)
+__global__ __launch_bounds__(256) void pool_frag_child_row(PoolArgs a)
 {
     using TO = typename std::conditional<BF, uint16_t, float>::type;
     using TI = typename std::conditional<IN_F32, float, TO>::type;
@@ -313,7 +313,7 @@ hipError_t go_k(const PoolArgs &a, int grid, hipStream_t s)
     if (a.ky == KY && a.kx == KX) return go_rows<KY, KX, BF, IN_F32, V>(a, s);
     FS_POOL_ROWS(FS_POOL_CASE)
 #undef FS_POOL_CASE
-    hipLaunchKernelGGL((pool_frag<BF, IN_F32, V>), dim3(grid), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((pool_frag_child_row<BF, IN_F32, V>), dim3(grid), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
@@ -353,7 +353,7 @@ std::string pool_kernel_name(int dtype, bool in_f32, int ky, int kx, int sy, int
     }
     FS_POOL_ROWS(FS_POOL_NAME)
 #undef FS_POOL_NAME
-    snprintf(buf, sizeof buf, "pool_frag<%s, %s, %d>", t, ti, v);
+    snprintf(buf, sizeof buf, "pool_frag_child_row<%s, %s, %d>", t, ti, v);
     return buf;
 }
 

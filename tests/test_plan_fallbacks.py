@@ -157,3 +157,14 @@ def test_small_grid_pools_of_wide_layers(monkeypatch, cin, k, cout, p, side):
     monkeypatch.setenv("FRAGSCAN_RUN", "0")  # keeps the layer's own tile
     assert mid()["name"].startswith("conv_frag_mfma<4, 7, 2, 1, ")
     net.close()
+
+
+def test_pool_kernels_have_names_of_their_own(monkeypatch):
+    """Launch names (the profiler's) tell the row-band kernels from the one
+    that takes a child row per workgroup."""
+    monkeypatch.setenv("FRAGSCAN_POOL_FUSE", "0")
+    for (p, s), want in {(3, 3): "pool_frag_rows<", (3, 2): "pool_frag<", (5, 5): "pool_frag_child_row<",
+                         (5, 2): "pool_frag_child_row<"}.items():
+        net = _net([wl.conv(2, 1, 16), wl.pool(p, 16, stride=s), wl.fc(1, 16, 2, "softmax")])
+        assert net.launches(1, 60, 60)[1]["name"].startswith(want)
+        net.close()
