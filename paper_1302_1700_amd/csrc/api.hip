@@ -1159,22 +1159,23 @@ fs_status make_plan(const fs_net *net, int B, int H, int W, Plan &P, const View 
                 // workgroups the device needs for it
                 auto finish = [&](bool run, long long tiles, int &lds, int &gx) {
                     gx = (int)std::min<long long>((tiles + 7) / 8 * 8, kMaxGrid);
-                    // The 7 x 2 tile on float32 products with the fused head
-                    // ran 2-7% faster one workgroup per CU than two on
-                    // grids of at most 12 workgroups per CU (N4 on 512x512
-                    // and 2x512x512 images; 3-5% slower on larger grids):
-                    // pad its LDS to admit one.  Other tiles and the f16
-                    // products are faster at two (N4 mirrored 512x512,
-                    // split: 122 against 172 us; 16 -> 100 channels, 7 x 1,
-                    // 701x903: 89 against 106), except where the tiles that
-                    // hold pixels are no more than the CUs: two on one CU
-                    // leave another idle (900 fragments of one pixel or none,
-                    // 208 -> 100: 32 against 59 us; dense grids of a tile per
-                    // CU 0-5% faster).
-                    const bool own_tile = !L.hs && L.nb == 7 && L.wn == 2 && (long long)gx * L.gy <= 12LL * net->ncu;
-                    if (fused_here && net->ncu > 0 &&
-                        (own_tile || count_tiles(g, ky, kx, B, a.mt, net->ncu) <= net->ncu) &&
-                        conv_blocks_per_cu(net->dtype, g.is_image, L.mb, L.nb, L.wn, L.wk, L.vec, L.hs, run, lds) == 2)
+                    // Fused heads without the half-step walk whose tile fits
+                    // two workgroups per CU, on grids of at most 12 per CU:
+                    // padding the LDS to admit one was 2-7% faster for the
+                    // 7 x 2 tile (N4 on 512x512 and 2x512x512 images; 3-5%
+                    // slower on larger grids) and for any tile where many of
+                    // the tiles hold no pixel, since two on one CU leave
+                    // another idle (208 -> 100, 100 of 904 with pixels: 31
+                    // against 58 us; 240 -> 100 3x3, 450 of 904: 672 against
+                    // 842) or where each has a CU anyway (0-5%).  Other grids
+                    // and the half-step walk are faster at two (16 -> 100
+                    // channels, 7 x 1, 701x903: 89 against 106; N4 mirrored
+                    // 512x512, split: 122 against 172).
+                    const bool pad = fused_here && !L.hs && net->ncu > 0 && (long long)gx * L.gy <= 12LL * net->ncu &&
+                                     ((L.nb == 7 && L.wn == 2) || gx <= net->ncu ||
+                                      (!run && 4 * count_tiles(g, ky, kx, B, a.mt, gx) <= 3LL * gx));
+                    if (pad && conv_blocks_per_cu(net->dtype, g.is_image, L.mb, L.nb, L.wn, L.wk, L.vec, L.hs, run,
+                                                  lds) == 2)
                         lds = std::max(lds, (int)(kMaxLdsBytes / 2 + 1024));
                     // plan-only nets: 256 CUs, one workgroup each
                     const int bpc = net->ncu > 0 ? conv_blocks_per_cu(net->dtype, g.is_image, L.mb, L.nb, L.wn,
