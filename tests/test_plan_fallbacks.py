@@ -123,8 +123,8 @@ def test_small_grid_pools_by_fused_tiles(monkeypatch, p, side, fused):
 
 
 @pytest.mark.parametrize("cin,cout,p,px,side,fused", [
-    (16, 80, 2, 2, 300, True), (16, 224, 3, 3, 300, True), (48, 128, 4, 4, 300, False), (48, 128, 2, 3, 300, False),
-    (48, 100, 2, 2, 300, False), (48, 100, 8, 8, 300, False), (80, 112, 5, 5, 300, True), (80, 112, 5, 5, 90, False),
+    (16, 80, 2, 2, 300, True), (16, 224, 3, 3, 300, True), (48, 128, 4, 4, 300, False), (48, 128, 2, 3, 300, False), (48, 128, 4, 4, 90, True),
+    (48, 100, 2, 2, 300, False), (48, 100, 8, 8, 300, False), (80, 112, 5, 5, 300, True), (80, 112, 5, 5, 90, True),
     (80, 112, 8, 8, 300, True), (16, 224, 10, 10, 300, False), (48, 128, 10, 10, 90, False), (16, 64, 4, 4, 300, True)])
 def test_wide_half_step_pools(monkeypatch, cin, cout, p, px, side, fused):
     """bf16 half-step layers of more than 64 outputs (a separate pool before
