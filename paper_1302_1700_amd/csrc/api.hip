@@ -846,7 +846,10 @@ void small_grid_tile(const fs_net *net, int li, const Geo &in, int B, NetLayer &
 // pixel (2 c_out elem bytes).  At peak rates that pays when
 // c_in k^2 ov < elem * (peak FLOP/s / HBM bytes/s): every layer of the five
 // workloads except N4's 48 -> 48 convolutions, whose fused form measured
-// 10-35% slower.  FRAGSCAN_POOL_FUSE=1 / 0 forces it on / off.
+// 10-35% slower.  (Split layers are held to the same line, at the float32
+// peak: with products at a third of the time N4's fused layers still took 2-3%
+// longer, 8 x 1024^2 11.14 -> 11.46 ms, and the layers of few channels below it
+// are bound by memory either way.)  FRAGSCAN_POOL_FUSE=1 / 0 forces it on / off.
 // small: small_grid_tile chose 64-pixel tiles; there the count of fused tiles
 // decides (small_grid_fusion).
 bool want_pool_fusion(const fs_net *net, int li, const NetLayer &l, bool small)

@@ -41,8 +41,8 @@
 //     Half steps (HS; c_in a multiple of 16): a K step of 32 takes two
 //     16-channel groups of the (tap, group) sequence, which may lie at two
 //     taps, lanes g < 2 the first, g >= 2 the second.  bf16 layers with 16 or
-//     48 channels need no gather that way (N4 in bf16 on 512 x 512: 514 ->
-//     185 us a scan).  Float32 layers whose inputs a tanh bounds run on the
+//     48 channels need no gather that way (N4 in bf16 on 512 x 512: 527 ->
+//     162 us a scan).  Float32 layers whose inputs a tanh bounds run on the
 //     f16 matrix cores there: x = hi + lo and w = hi + lo as f16 pairs (scaled
 //     by powers of two; 23 significand bits each), hi hi + hi lo + lo hi
 //     accumulated in float32.  The float32 products cap a layer at 157
@@ -390,11 +390,15 @@ __device__ __forceinline__ void fused_head_finish(const ConvArgs &a, int b, int 
 }
 
 // RUN: run tiles (ConvArgs::run = 1, no fused pool); the other instances
-// take one band of one fragment per tile sequence.  Float32 tiles of one
-// channel block and up to four pixel blocks (16-channel layers, whose
-// launches wait on memory) are compiled for six workgroups per CU (at most
-// 80 registers: six waves per SIMD instead of five; 4-5% faster on the
-// 2x2 16 -> 16 + pool layers; larger tiles would spill).
+// take one band of one fragment per tile sequence.
+// Least workgroups per CU an instance is compiled for.  Float32 tiles of one
+// channel block and up to four pixel blocks (16-channel layers, whose launches
+// wait on memory) on float32 products: six (at most 80 registers: six waves
+// per SIMD instead of five; 4-5% faster on the 2x2 16 -> 16 + pool layers;
+// larger tiles would spill).  The same tiles in half steps hold two weight sets
+// of hi and lo: four (at six they spill; 3x3 and 2x2 16 -> 16 + pool of a
+// 2048^2 image 174 and 147 us at four, 178 and 152 left to the compiler, 921
+// and 591 at six).  Larger half-step tiles: two, all their registers allow.
 constexpr int min_blocks(int mb, int nb, bool bf, bool hs)
 {
     if (!bf && nb == 1 && mb <= 4) return hs ? 4 : 6;
@@ -402,8 +406,12 @@ constexpr int min_blocks(int mb, int nb, bool bf, bool hs)
 }
 
 // Weight register sets of the half-step walk: enough steps ahead that their
-// products (16 cycles each) cover the ~1000 cycles of a load, where registers
-// are not what limits the waves per SIMD.
+// products (16 cycles each, three per block in float32) cover the ~1000 cycles
+// of a load: one from 12 blocks on (a second set costs the 4 x 3 and 4 x 7
+// tiles waves or spills: N4's 4x4 layers on 1024^2 210 -> 244 us, FC1 365 ->
+// 792), two from 336 cycles a step, four below.  4 x 1 tiles take two: with
+// four a bf16 wave per SIMD less fits (5 instead of 6), and the 3x3 16 -> 16 +
+// pool layers of a 2048^2 image went from 174 and 186 to 181 and 193 us.
 constexpr int half_step_ring(int mb, int nb, bool bf)
 {
     const int cycles = mb * nb * 16 * (bf ? 1 : 3);
