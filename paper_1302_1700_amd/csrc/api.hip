@@ -1752,15 +1752,19 @@ static fs_status net_create(const fs_layer *layers, int32_t n_layers, int32_t in
     // --- pack parameters into one device block ---
     std::vector<uint8_t> blob;
     {
-        // room for all of it (weights of float32 layers in both packings, over
-        // 64 channels padded to tiles of up to 14 blocks): growing the block
-        // layer by layer copied it each time (N4: 1.74 -> 0.72 ms a net with
-        // that and the split's conversions vectorised)
-        size_t room = 1 << 18;
+        // about what all of it takes, weights of split layers in both
+        // packings: growing the block layer by layer copied it each time (N4:
+        // 1.76 -> 0.68 ms a net with that and the split's conversions
+        // vectorised)
+        const size_t per_weight = dtype == FS_BF16 ? 2 : L.back().act == FS_ACT_SOFTMAX ? 8 : 4;
+        size_t room = 4096;
         for (const NetLayer &l : L)
-            if (l.kind != FS_MAXPOOL)
-                room += ((size_t)l.cin * l.k * l.kx + 32) * (align_up(l.cout, 16) + (l.cout > 64 ? 208 : 0)) *
-                        (dtype == FS_F32 ? 8 : 2);
+            if (l.kind != FS_MAXPOOL) {
+                int nb, wn;
+                const int nbt0 = (l.cout + 15) / 16;
+                choose_channel_tile(nbt0, true, &nb, &wn);
+                room += (align_up((size_t)l.cin * l.k * l.kx, 32) * per_weight + 64) * align_up(nbt0, nb * wn) * 16 + 2048;
+            }
         blob.reserve(room);
     }
     auto grow = [&](size_t n) {  // n zeroed bytes
