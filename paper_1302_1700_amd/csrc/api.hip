@@ -893,12 +893,15 @@ bool small_grid_fusion(const fs_net *net, const NetLayer &l, const NetLayer &p, 
 // took several): outputs in whole 16-byte chunks, and of the windows with a
 // row-band kernel those whose fused walk is separable, the rest up to one tile
 // per CU, of the others those whose halo takes less than 16 times the separate
-// tiles.  Us, convolution + separate pool / fused (fused over separate tiles):
+// tiles, and less than 6000 / K times (the fused launch runs its tiles at the
+// convolution's pace).  Us, convolution + separate pool / fused (fused over
+// separate tiles):
 //   16 -> 80 2x2, 800^2: 2x2 74.8 / 60.9, 3x3 75.0 / 74.0, 4x4 77.6 / 159 (90^2: 11.9 / 10.9);
 //   48 -> 100 3x3, 300^2 (chunks of 4): 2x2 33.0 / 61.4, 3x3 35.4 / 75.7, 4x4 36.2 / 156;
 //   80 -> 112 2x2, 800^2: 5x5 603 / 249, 8x8 1380 / 514 (4), 10x10 2005 / 1237 (15.7);
 //   ... 90^2: 5x5 20.1 / 25.1, 6x6 22.0 / 26.3 (and a launch less: even a scan);
-//   48 -> 128 3x3, 300^2: 6x6 96 / 98 (7.9), 8x8 175 / 175 (13.6), 10x10 204 / 464 (39.6).
+//   48 -> 128 3x3, 300^2: 6x6 96 / 98 (7.9), 8x8 175 / 175 (13.6), 10x10 204 / 464 (39.6);
+//   80 -> 176 3x5 (K = 1200), 451x458: 8x8 359 / 1142 (16).
 bool wide_half_fusion(const fs_net *net, const NetLayer &l, const NetLayer &p, const Geo &in, int B, int mt,
                       long long tiles)
 {
@@ -906,7 +909,8 @@ bool wide_half_fusion(const fs_net *net, const NetLayer &l, const NetLayer &p, c
     if (l.cout % 8) return false;
     if (pool_has_row_bands(p.k, p.kx))
         return (p.k == p.kx && p.k <= 3) || tiles <= (net->ncu > 0 ? net->ncu : 256);
-    return tiles <= 16 * count_tiles(in, l.k, l.kx, B, mt, tiles);
+    const long long separate = count_tiles(in, l.k, l.kx, B, mt, tiles);
+    return tiles <= 16 * separate && (long long)l.cin * l.k * l.kx * tiles <= 6000 * separate;
 }
 
 // First output coordinate (along one axis) of the final fragments' axis

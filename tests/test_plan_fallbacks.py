@@ -168,3 +168,13 @@ def test_pool_kernels_have_names_of_their_own(monkeypatch):
         net = _net([wl.conv(2, 1, 16), wl.pool(p, 16, stride=s), wl.fc(1, 16, 2, "softmax")])
         assert net.launches(1, 60, 60)[1]["name"].startswith(want)
         net.close()
+
+
+def test_wide_half_step_pools_by_work():
+    """A halo of many tiles is not recomputed over a long K walk."""
+    layers = [wl.conv(2, 1, 80), wl.pool(3, 80), wl.conv(3, 80, 176, kx=5), wl.pool(8, 176), wl.fc(1, 176, 48),
+              wl.fc(1, 48, 2, "softmax")]
+    net = _net(layers, "bf16")
+    names = {L["layer"]: L["name"] for L in net.launches(1, 451, 458)}
+    net.close()
+    assert "+pool" not in names[2] and names[3].startswith("pool_frag_child_row<"), names
