@@ -1173,12 +1173,19 @@ fs_status make_plan(const fs_net *net, int B, int H, int W, Plan &P, const View 
                     // the tiles hold no pixel, since two on one CU leave
                     // another idle (208 -> 100, 100 of 904 with pixels: 31
                     // against 58 us; 240 -> 100 3x3, 450 of 904: 672 against
-                    // 842) or where each has a CU anyway (0-5%).  Other grids
-                    // and the half-step walk are faster at two (16 -> 100
-                    // channels, 7 x 1, 701x903: 89 against 106; N4 mirrored
-                    // 512x512, split: 122 against 172).
+                    // 842), where each has a CU anyway (0-5%), or where two
+                    // per CU leave half a round empty (a float32 round of two
+                    // takes 1.6 to 2 of one: 48 -> 100 3x3, 736 tiles in three
+                    // rounds 155 us, in two 200; 16 -> 112 4x4 99 and 124; 1x1
+                    // and 2x2 39 and 42, 41 and 42).  Other grids and the
+                    // half-step walk are faster at two (16 -> 100 channels,
+                    // 7 x 1, 701x903: 89 against 106; N4 mirrored 512x512,
+                    // split: 122 against 172).
+                    const long long ncu1 = net->ncu > 0 ? net->ncu : 256;
+                    const long long rounds1 = (gx + ncu1 - 1) / ncu1, rounds2 = (gx + 2 * ncu1 - 1) / (2 * ncu1);
                     const bool pad = fused_here && !L.hs && net->ncu > 0 && (long long)gx * L.gy <= 12LL * net->ncu &&
                                      ((L.nb == 7 && L.wn == 2) || gx <= net->ncu ||
+                                      (net->dtype == DT_F32 && 10 * rounds1 < 16 * rounds2) ||
                                       (!run && 4 * count_tiles(g, ky, kx, B, a.mt, gx) <= 3LL * gx));
                     if (pad && conv_blocks_per_cu(net->dtype, g.is_image, L.mb, L.nb, L.wn, L.wk, L.vec, L.hs, run,
                                                   lds) == 2)

@@ -66,9 +66,10 @@ def test_wide_layers_with_pools_on_small_grids(fsb, cin, cout, p, more):
     assert any(", 7, 2, 1, " in n and "+pool" in n for n in names), names
 
 
-def test_sparse_head_grids_take_a_cu_each(fsb):
-    """A fused head whose tiles that hold pixels are no more than the CUs runs
-    one workgroup per CU, on larger grids as many as fit."""
+def test_head_grids_that_take_a_cu_each(fsb):
+    """Float32 fused heads run one workgroup per CU where a quarter of the
+    tiles hold no pixel, or where two would leave half a round empty; on other
+    grids as many as fit."""
     layers = [wl.conv(4, 1, 32), wl.pool(8, 32, stride=5), wl.pool(2, 32), wl.conv(4, 32, 208), wl.pool(3, 208),
               wl.fc(1, 208, 100), wl.fc(1, 100, 2, "none")]
     params = wl.make_weights(layers, 7, 0.05)
@@ -77,6 +78,13 @@ def test_sparse_head_grids_take_a_cu_each(fsb):
     net.close()
     assert sparse["name"] == dense["name"] and "+head" in sparse["name"], (sparse, dense)
     assert (sparse["per_cu"], dense["per_cu"]) == (1, 2), (sparse, dense)
+    layers = [wl.conv(2, 1, 48), wl.pool(3, 48), wl.fc(3, 48, 100), wl.fc(1, 100, 2, "none")]
+    net = fsb.Net(layers, wl.make_weights(layers, 7, 0.05), 1)
+    heads = {H: net.launches(1, H, H + 3)[-1] for H in (300, 420, 510)}
+    net.close()
+    rounds = {H: -(-L["grid"] // 256) for H, L in heads.items()}
+    assert [rounds[H] for H in (300, 420, 510)] == [2, 3, 5], rounds
+    assert {H: L["per_cu"] for H, L in heads.items()} == {300: 2, 420: 1, 510: 2}, heads
 
 
 @pytest.mark.parametrize("act", ["tanh", "none"])
