@@ -1321,7 +1321,9 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
                              q < a.nfrag && ybar < hc && xbar < wc && ybar < a.pool_oh && xbar < a.pool_ow,
                              DBG_FUSED_POOL);
         };
-        if ((a.cout % TPAD) == 0) {
+        // (expected, which keeps the other walk's code out of the way: bf16 2x3
+        // and 3x2 pools of 72x325 images 2% slower with it in between)
+        if (__builtin_expect((a.cout % TPAD) == 0, 1)) {
             // A thread owns one 16-byte channel chunk v of one filter column
             // c and walks a run of consecutive filter rows, so its LDS source
             // and child addresses only advance: a row down in the tile, and
@@ -1430,21 +1432,25 @@ __global__ __launch_bounds__(256, min_blocks(MB, NB, BF, HS)) void conv_frag_mfm
                 const TC *src = tile + __mul24(__mul24(r, ew) + c, TS) + ch;
                 TC m = src[0];
                 if constexpr (BF) {
-                    // two window pixels at a time, one in each half (two loads
-                    // in flight; 32 -> 100 + 8x8 pool: 259 -> 159 us)
-                    auto max2 = [](uint32_t x, uint32_t y) {
-                        return KEYS ? max_i16x2(x, y) : max_bf16x2_bounded(x, y);
-                    };
-                    uint32_t m2 = m * 0x10001u;
-                    for (int i = 0; i < kpy; ++i) {
-                        const TC *row = src + __mul24(__mul24(i, ew), TS);
-                        int j = 0;
-                        for (; j + 1 < kpx; j += 2)
-                            m2 = max2(m2, row[__mul24(j, TS)] | (uint32_t)row[__mul24(j + 1, TS)] << 16);
-                        if (j < kpx) m2 = max2(m2, row[__mul24(j, TS)] * 0x10001u);
+                    if constexpr (KEYS) {
+                        for (int i = 0; i < kpy; ++i)
+                            for (int j = 0; j < kpx; ++j)
+                                m = (TC)max_i16x2(m, src[__mul24(__mul24(i, ew) + j, TS)]);  // keys in the low half
+                        m = (TC)bf16x2_key(m);
+                    } else {
+                        // two window pixels at a time, one in each half, as the
+                        // compiler takes the keys by itself (two loads in flight;
+                        // 32 -> 100 + 8x8 pool: 259 -> 159 us)
+                        uint32_t m2 = m * 0x10001u;
+                        for (int i = 0; i < kpy; ++i) {
+                            const TC *row = src + __mul24(__mul24(i, ew), TS);
+                            int j = 0;
+                            for (; j + 1 < kpx; j += 2)
+                                m2 = max_bf16x2_bounded(m2, row[__mul24(j, TS)] | (uint32_t)row[__mul24(j + 1, TS)] << 16);
+                            if (j < kpx) m2 = max_bf16x2_bounded(m2, row[__mul24(j, TS)] * 0x10001u);
+                        }
+                        m = (TC)max_bf16x2_bounded(m2, m2 >> 16);
                     }
-                    m2 = max2(m2, m2 >> 16);
-                    m = (TC)(KEYS ? bf16x2_key(m2) : m2);
                 } else {
                     for (int i = 0; i < kpy; ++i)
                         for (int j = 0; j < kpx; ++j) m = fmaxf(m, src[__mul24(__mul24(i, ew) + j, TS)]);
